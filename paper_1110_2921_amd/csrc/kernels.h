@@ -409,9 +409,10 @@ constexpr SymLayout sym_layout(int p) {
 // source - target, largest >= 2), packed rx | ry << 2 | rz << 4 | G << 6 | Z << 9
 // with G the axes of the orbit's reflections and Z the axes where r_a = 0.
 constexpr int kSymOrbits = 56;
-// coarsest level the orbit kernel runs (coarser levels have too few target cells
-// to fill the chip without splitting every workgroup down to one orbit)
-constexpr int kSymMinLevel = 4;
+// finest level of the orbit form for few cells (launch_m2l_orbits); the finer ones
+// run the kernels that share the operators of 64 targets in LDS: at level 4 those
+// take 456 us (FP64, p = 8), the form for few cells 813 us
+constexpr int kSymMaxSmall = 3;
 
 // Mc[cell][3][16 nblk] (FP32) from the standard-layout multipoles of `ncells`
 // cells (M[cell][3][kp]): mc_src[16 k + q] is the standard index held at
@@ -443,6 +444,17 @@ bool m2l_sym_supported(int p);
 hipError_t launch_m2l_sym(hipStream_t s, int level, int periodic, int p, int kp, const float *mc, int64_t zero_cell,
                           const float *ops, const int32_t *op_off, const int32_t *orbits, const int16_t *row_std,
                           float *dst, int accumulate, float *part, size_t part_elems);
+
+// M2L of the levels lo .. hi (<= kSymMaxSmall) of a uniform tree by reflection
+// orbits in one launch: dst (locals of all levels, standard layout) is
+// overwritten (rows < C) from the class-major multipoles mc of all levels
+// (zero_cell the index of their zero cell).  Operators and offsets: those of
+// launch_m2l_sym (FP32) or launch_m2l_sym64 (FP64), with 64 readable elements
+// past the end of `ops`.
+template <typename T>
+hipError_t launch_m2l_orbits(hipStream_t s, int lo, int hi, int periodic, int p, int kp, const T *mc,
+                             int64_t zero_cell, const T *ops, const int32_t *op_off, const int32_t *orbits,
+                             const int16_t *row_std, T *dst);
 
 // Targets and sources of one level of an adaptive tree for the FP64 orbit
 // M2L: the level's cells grouped by octant, tcell[oct_base[o] ..] of oct_n[o]

@@ -507,9 +507,240 @@ __global__ void __launch_bounds__(kSymThreads) k_m2l_sym64(int level, int period
     });
 }
 
+// The orbit form for the coarse levels, whose few cells cannot share an operator
+// in LDS: every level from `lo` to `hi` in one launch, and no partial sums in
+// memory.  A workgroup takes 16 columns (target, component) of one level's
+// octant and one of RS shares of the row blocks; its 8 waves take every
+// eighth orbit each, with the operator blocks read from L2 straight into the
+// MFMA's A registers and the next step's operator blocks and sources in flight
+// during the current step's MFMAs; the waves' sums meet in LDS, in wave order.
+// Bound by the vector L1 (each wave reads its own operator blocks, 64 B a cycle and
+// CU), not by MFMA; two shares of the row blocks put twice the waves on the few
+// tiles (one share: 106 against 88 us, three: 145, FP32 levels 1 to 3).
+// Levels 1 to 3, periodic: p = 10 FP32 88 us, FP64 269 us, p = 8 FP64 136 us; the
+// dense operators, 189 offsets split over workgroups and their partial sums
+// added by a second launch per level, took 510, 497 and 432 us.
+// FP32: a step is a k block (four k steps); FP64: half a block.
+template <typename T> struct Step;
+template <> struct Step<float> {
+    typedef float V __attribute__((ext_vector_type(4)));
+    typedef float Acc __attribute__((ext_vector_type(4)));
+    static constexpr int VN = 4;
+    static __device__ __forceinline__ Acc mfma(float a, float b, Acc c) {
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+    }
+    static __device__ __forceinline__ int row(int h, int r) { return 4 * h + r; }
+};
+template <> struct Step<double> {
+    typedef double V __attribute__((ext_vector_type(2)));
+    typedef double Acc __attribute__((ext_vector_type(4)));
+    static constexpr int VN = 2;
+    static __device__ __forceinline__ Acc mfma(double a, double b, Acc c) {
+        return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+    }
+    static __device__ __forceinline__ int row(int h, int r) { return h + 4 * r; }
+};
+
+constexpr int kOrbWaves = 8;
+constexpr int kOrbThreads = 64 * kOrbWaves;
+
+struct OrbLevels {
+    int lo, hi;            // levels of the launch
+    int tile0[8];          // first workgroup of level lo + i
+};
+
+// steps of an orbit: (k block, half)
+template <typename T, int P>
+struct OrbSteps {
+    static constexpr SymLayout SL = sym_layout(P);
+    static constexpr int halves(int b) { return Step<T>::VN == 2 && SL.bsteps[b] > 2 ? 2 : 1; }
+    static constexpr int count() {
+        int n = 0;
+        for (int b = 0; b < SL.nblk; ++b) n += halves(b);
+        return n;
+    }
+    static constexpr int block(int s) {
+        int b = 0;
+        while (s >= halves(b)) s -= halves(b++);
+        return b;
+    }
+    static constexpr int half(int s) {
+        int b = 0;
+        while (s >= halves(b)) s -= halves(b++);
+        return s;
+    }
+};
+
+template <typename T, int P, int A0, int A1>
+__device__ __forceinline__ void orbits_body(const OrbLevels &lv, int periodic, int kp, const T *__restrict__ mc,
+                                            uint32_t zero_off, const T *__restrict__ ops,
+                                            const int32_t *__restrict__ op_off, int op_stride, int op_octant,
+                                            const int32_t *__restrict__ orbits,
+                                            const int16_t *__restrict__ row_std, T *__restrict__ dst, T *red) {
+    using S = Step<T>;
+    using V = typename S::V;
+    using OS = OrbSteps<T, P>;
+    constexpr SymLayout SL = sym_layout(P);
+    constexpr int NB = SL.nblk, KC = 16 * NB, CELL = 3 * KC, NA = A1 - A0, NS = OS::count();
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int h = lane >> 4, col = lane & 15;
+    int level = lv.lo, b = int(blockIdx.x);
+    while (level < lv.hi && b >= lv.tile0[level + 1 - lv.lo]) ++level;
+    b -= lv.tile0[level - lv.lo];
+    const int octant = b & 7;
+    const int j = (b >> 3) * 16 + col, side = 1 << level;
+    const int slot = j / 3, comp = j - 3 * slot;
+    const bool tvalid = slot < (1 << (3 * (level - 1)));
+    const uint32_t tkey = tvalid ? (uint32_t(slot) << 3) | uint32_t(octant) : 0u;
+    const int tc[3] = {int(compact3(tkey)), int(compact3(tkey >> 1)), int(compact3(tkey >> 2))};
+    const size_t base = ((size_t(1) << (3 * level)) - 1) / 7;   // the level's first cell
+    const uint32_t base_off = uint32_t(base) * uint32_t(CELL) + uint32_t(comp * KC + 4 * h);
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<T *>(mc), 0, -1, 0x00020000);
+
+    uint32_t mo[8];   // byte offsets of the orbit's member sources (absent: the zero cell)
+    auto members = [&](int info) {
+        const int G = (info >> 6) & 7;
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+            bool ok = tvalid && !(r & ~G);
+            uint32_t key = 0;
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                const int rep = (info >> (2 * a)) & 3;
+                int d = ((r >> a) & 1) ? -rep : rep;
+                if ((octant >> a) & 1) d = -d;
+                int c = tc[a] + d;
+                if (periodic) c &= side - 1;
+                else ok = ok && c >= 0 && c < side;
+                key |= spread3(uint32_t(c)) << a;
+            }
+            mo[r] = (ok ? base_off + key * uint32_t(CELL) : zero_off + uint32_t(4 * h)) * uint32_t(sizeof(T));
+        }
+    };
+    // step s of the orbit whose operator starts at op (Z: its zero axes); off
+    // walks over the column blocks' compact storage
+    auto load = [&](auto si, const T *op, int Z, int &off, V (&v)[8], V (&a)[NA]) {
+        constexpr int s = decltype(si)::value, B = OS::block(s), HALF = OS::half(s);
+        const uint32_t cb = uint32_t((16 * B + S::VN * HALF) * sizeof(T));
+#pragma unroll
+        for (int r = 0; r < 8; ++r)
+            v[r] = __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(rsrc, int(mo[r] + cb), 0, 0));
+        int o = off;
+        static_for<8>([&](auto xi) {
+            constexpr int X = decltype(xi)::value;
+            static_for<NB>([&](auto ai) {
+                constexpr int A = decltype(ai)::value;
+                if constexpr (SL.bcls[A] == (SL.bcls[B] ^ X)) {
+                    const bool on = !(X & Z);
+                    if constexpr (A >= A0 && A < A1)
+                        a[A - A0] = *reinterpret_cast<const V *>(
+                            op + (on ? o : 0) + S::VN * ((HALF * 4 + h) * SL.bnv[A] + col));
+                    o += on ? 16 * SL.bnv[A] : 0;
+                }
+            });
+        });
+        if constexpr (HALF + 1 == OS::halves(B)) off = o;   // the block's last step
+    };
+    typename S::Acc acc[NA];
+#pragma unroll
+    for (int i = 0; i < NA; ++i) acc[i] = typename S::Acc{T(0), T(0), T(0), T(0)};
+
+    const int32_t *oo = op_off + octant * op_octant;
+    V v[8], a[NA];
+    int o = wave, info = orbits[wave], off = 0;
+    const T *op = ops + oo[wave * op_stride];
+    members(info);
+    load(std::integral_constant<int, 0>{}, op, (info >> 9) & 7, off, v, a);
+    for (; o < kSymOrbits; o += kOrbWaves) {
+        const int Z = (info >> 9) & 7;
+        const int on = o + kOrbWaves < kSymOrbits ? o + kOrbWaves : o;
+        const int info_n = orbits[on];
+        const T *op_n = ops + oo[on * op_stride];
+        static_for<NS>([&](auto si) {
+            constexpr int s = decltype(si)::value, B = OS::block(s), HALF = OS::half(s);
+            V vn[8], an[NA];
+            if constexpr (s + 1 < NS) {
+                load(std::integral_constant<int, s + 1>{}, op, Z, off, vn, an);
+            } else {
+                members(info_n);
+                off = 0;
+                load(std::integral_constant<int, 0>{}, op_n, (info_n >> 9) & 7, off, vn, an);
+            }
+            // Walsh-Hadamard transform over the members (absent ones are zero)
+#pragma unroll
+            for (int bit = 1; bit < 8; bit <<= 1)
+#pragma unroll
+                for (int r = 0; r < 8; ++r)
+                    if (!(r & bit)) {
+                        const V x = v[r], y = v[r | bit];
+                        v[r] = x + y;
+                        v[r | bit] = x - y;
+                    }
+            static_for<NA>([&](auto ai) {
+                constexpr int A = A0 + decltype(ai)::value, X = SL.bcls[A] ^ SL.bcls[B];
+                if (!(X & Z))
+                    static_for<S::VN>([&](auto ki) {
+                        constexpr int K = decltype(ki)::value;
+                        if constexpr (S::VN * HALF + K < SL.bsteps[B])
+                            acc[A - A0] = S::mfma(a[A - A0][K], v[X][K], acc[A - A0]);
+                    });
+            });
+#pragma unroll
+            for (int r = 0; r < 8; ++r) v[r] = vn[r];
+#pragma unroll
+            for (int i = 0; i < NA; ++i) a[i] = an[i];
+        });
+        info = info_n;
+        op = op_n;
+    }
+    // the waves' sums, a row block at a time: thread tid sums element tid / 16 (its
+    // row) of column tid % 16 -- written as [wave][lane][r]
+    static_for<NA>([&](auto ai) {
+        constexpr int A = A0 + decltype(ai)::value;
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < 4; ++r) red[(wave * 64 + lane) * 4 + r] = acc[A - A0][r];
+        __syncthreads();
+        if (tid < 256) {
+            const int l = tid >> 2, r = tid & 3;
+            const int e = S::row(l >> 4, r);
+            T x = T(0);
+#pragma unroll
+            for (int w = 0; w < kOrbWaves; ++w) x += red[(w * 64 + l) * 4 + r];
+            const int jl = (b >> 3) * 16 + (l & 15), sl = jl / 3, cl = jl - 3 * sl;
+            if (e < SL.bnv[A] && sl < (1 << (3 * (level - 1))))
+                dst[((base + ((size_t(sl) << 3) | octant)) * 3 + cl) * kp + row_std[16 * A + e]] = x;
+        }
+    });
+}
+
+// row blocks of share i of RS
+constexpr int orb_row0(int nb, int rs, int i) { return i * nb / rs; }
+
+template <typename T, int P, int RS>
+__global__ void __launch_bounds__(kOrbThreads) k_m2l_orbits(OrbLevels lv, int periodic, int kp,
+                                                            const T *__restrict__ mc, uint32_t zero_off,
+                                                            const T *__restrict__ ops,
+                                                            const int32_t *__restrict__ op_off, int op_stride,
+                                                            int op_octant, const int32_t *__restrict__ orbits,
+                                                            const int16_t *__restrict__ row_std,
+                                                            T *__restrict__ dst) {
+    __shared__ T red[kOrbWaves * 256];
+    constexpr int NB = sym_layout(P).nblk;
+    static_assert(NB > 0 && RS <= 4, "degree without a class layout");
+    static_for<RS>([&](auto ri) {
+        constexpr int R = decltype(ri)::value;
+        if (int(blockIdx.y) == R)
+            orbits_body<T, P, orb_row0(NB, RS, R), orb_row0(NB, RS, R + 1)>(lv, periodic, kp, mc, zero_off, ops,
+                                                                           op_off, op_stride, op_octant, orbits,
+                                                                           row_std, dst, red);
+    });
+}
+
 }  // namespace
 
-bool m2l_sym_supported(int p) { return p == 10; }
+bool m2l_sym_supported(int p) { return p == 6 || p == 8 || p == 10; }
 
 template <typename T>
 hipError_t launch_sym_pack_range(hipStream_t s, int64_t npack, int64_t zero_cell, int kp, int kc, const T *M,
@@ -532,20 +763,60 @@ template hipError_t launch_sym_pack_range<float>(hipStream_t, int64_t, int64_t, 
 template hipError_t launch_sym_pack_range<double>(hipStream_t, int64_t, int64_t, int, int, const double *,
                                                   const int16_t *, double *);
 
-hipError_t launch_m2l_sym64(hipStream_t s, int level, int periodic, int p, int kp, const double *mc,
-                            int64_t zero_cell, const double *ops, const int32_t *sl_off, const int32_t *orbits,
-                            const int16_t *row_std, double *dst, int accumulate, double *part, size_t part_elems) {
-    if (!m2l_sym_supported(p) || level < 1) return hipErrorInvalidValue;
-    constexpr SymLayout SL = sym_layout(10);
+// f(std::integral_constant<int, P>) for the degrees the kernels are built for
+template <typename F>
+hipError_t with_degree(int p, F &&f) {
+    switch (p) {
+    case 6: return f(std::integral_constant<int, 6>{});
+    case 8: return f(std::integral_constant<int, 8>{});
+    case 10: return f(std::integral_constant<int, 10>{});
+    default: return hipErrorInvalidValue;
+    }
+}
+
+// Orbit ranges a launch of `tiles` workgroups is split into: a workgroup holds a
+// compute unit (its LDS), so the launch takes ceil(tiles nsplit / CUs) rounds of
+// ceil(56 / nsplit) orbits; the smallest nsplit with the fewest orbit-rounds
+// that the partial-sum buffer (part_elems, per_split each) holds.  Level 4
+// (64 tiles) takes 4 ranges, one round of 14 orbits: 301 us FP32 and 527 us FP64 at
+// p = 10 (354 and 718 us with ranges enough for 1024 workgroups, whose prologues
+// and second rounds cost more than they fill).
+static int orbit_splits(int tiles, size_t per_split, size_t part_elems) {
+    static const int ncu = [] {
+        int dev = 0, v = 0;
+        if (hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v < 1)
+            v = 256;
+        return v;
+    }();
+    int nsplit = 1;
+    int64_t best = -1;
+    for (int ns = 1; ns <= kSymOrbits && size_t(ns) * per_split <= part_elems; ++ns) {
+        const int64_t rounds = (int64_t(tiles) * ns + ncu - 1) / ncu;
+        const int64_t cost = rounds * ((kSymOrbits + ns - 1) / ns);
+        if (best < 0 || cost < best) {
+            best = cost;
+            nsplit = ns;
+        }
+    }
+    return nsplit;
+}
+
+template <int P>
+hipError_t m2l_sym64(hipStream_t s, int level, int periodic, int kp, const double *mc, int64_t zero_cell,
+                     const double *ops, const int32_t *sl_off, const int32_t *orbits, const int16_t *row_std,
+                     double *dst, int accumulate, double *part, size_t part_elems) {
+    if (level < 1) return hipErrorInvalidValue;
+    constexpr SymLayout SL = sym_layout(P);
     constexpr int KC = 16 * SL.nblk;
     if ((uint64_t(zero_cell) + 1) * 3 * KC * sizeof(double) > (uint64_t(1) << 32)) return hipErrorInvalidValue;
     const int64_t ncell_t = int64_t(1) << (3 * (level - 1));
     const size_t smem = sizeof(double) * size_t(kRing) * size_t(16 * SL.C + 32);
-    int nsplit = part ? translate_splits(level, kSymTargets, kp, part_elems) : 1;
-    if (nsplit > kSymOrbits) nsplit = kSymOrbits;
+    const int tiles = int((ncell_t + kSymTargets - 1) / kSymTargets) * 8;
+    const int nsplit = part ? orbit_splits(tiles, size_t(ncell_t) * 8 * 3 * kp, part_elems) : 1;
     double *pbuf = nsplit > 1 ? part : nullptr;
-    const dim3 grid(unsigned((ncell_t + kSymTargets - 1) / kSymTargets * 8), unsigned(nsplit));
-    hipLaunchKernelGGL((k_m2l_sym64<10, false>), grid, dim3(kSymThreads), smem, s, level, periodic, kp, mc,
+    const dim3 grid{unsigned(tiles), unsigned(nsplit)};
+    hipLaunchKernelGGL((k_m2l_sym64<P, false>), grid, dim3(kSymThreads), smem, s, level, periodic, kp, mc,
                        uint32_t(zero_cell * 3 * KC), ops, sl_off, orbits, row_std, dst, accumulate, nsplit, pbuf,
                        SymAdapt());
     hipError_t e = hipGetLastError();
@@ -553,12 +824,20 @@ hipError_t launch_m2l_sym64(hipStream_t s, int level, int periodic, int p, int k
     return launch_split_reduce64(s, level, kp, SL.C, nsplit, pbuf, dst, accumulate);
 }
 
-hipError_t launch_m2l_sym64_adaptive(hipStream_t s, int p, int kp, const double *mc, int64_t zero_cell,
-                                     const double *ops, const int32_t *sl_off, const int32_t *orbits,
-                                     const int16_t *row_std, double *dst, int accumulate, const SymAdapt &ad_in,
-                                     double *part, size_t part_elems) {
-    if (!m2l_sym_supported(p)) return hipErrorInvalidValue;
-    constexpr SymLayout SL = sym_layout(10);
+hipError_t launch_m2l_sym64(hipStream_t s, int level, int periodic, int p, int kp, const double *mc,
+                            int64_t zero_cell, const double *ops, const int32_t *sl_off, const int32_t *orbits,
+                            const int16_t *row_std, double *dst, int accumulate, double *part, size_t part_elems) {
+    return with_degree(p, [&](auto pc) {
+        return m2l_sym64<decltype(pc)::value>(s, level, periodic, kp, mc, zero_cell, ops, sl_off, orbits, row_std, dst,
+                                              accumulate, part, part_elems);
+    });
+}
+
+template <int P>
+hipError_t m2l_sym64_adaptive(hipStream_t s, int kp, const double *mc, int64_t zero_cell, const double *ops,
+                              const int32_t *sl_off, const int32_t *orbits, const int16_t *row_std, double *dst,
+                              int accumulate, const SymAdapt &ad_in, double *part, size_t part_elems) {
+    constexpr SymLayout SL = sym_layout(P);
     constexpr int KC = 16 * SL.nblk;
     if ((uint64_t(zero_cell) + 1) * 3 * KC * sizeof(double) > (uint64_t(1) << 32)) return hipErrorInvalidValue;
     SymAdapt ad = ad_in;
@@ -566,33 +845,12 @@ hipError_t launch_m2l_sym64_adaptive(hipStream_t s, int p, int kp, const double 
     for (int o = 0; o < 8; ++o) ad.tile_start[o + 1] = ad.tile_start[o] + (ad.oct_n[o] + kSymTargets - 1) / kSymTargets;
     const int grid = ad.tile_start[8];
     if (grid == 0) return hipSuccess;
-    // orbit-range splits: a workgroup holds a compute unit (its LDS), so the
-    // level takes ceil(grid nsplit / CUs) rounds of ceil(56 / nsplit) orbits;
-    // the smallest nsplit with the fewest orbit-rounds that the partial-sum
-    // buffer holds
-    int nsplit = 1;
-    if (part != nullptr && ad.part_cells > 0) {
-        static int ncu = 0;
-        if (ncu == 0) {
-            int dev = 0;
-            if (hipGetDevice(&dev) != hipSuccess ||
-                hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || ncu < 1)
-                ncu = 256;
-        }
-        const size_t per_split = size_t(ad.part_cells) * 3 * kp;
-        int64_t best = -1;
-        for (int ns = 1; ns <= kSymOrbits && size_t(ns) * per_split <= part_elems; ++ns) {
-            const int64_t rounds = (int64_t(grid) * ns + ncu - 1) / ncu;
-            const int64_t cost = rounds * ((kSymOrbits + ns - 1) / ns);
-            if (best < 0 || cost < best) {
-                best = cost;
-                nsplit = ns;
-            }
-        }
-    }
+    const int nsplit = part != nullptr && ad.part_cells > 0
+                           ? orbit_splits(grid, size_t(ad.part_cells) * 3 * kp, part_elems)
+                           : 1;
     double *pbuf = nsplit > 1 ? part : nullptr;
     const size_t smem = sizeof(double) * size_t(kRing) * size_t(16 * SL.C + 32);
-    hipLaunchKernelGGL((k_m2l_sym64<10, true>), dim3(unsigned(grid), unsigned(nsplit)), dim3(kSymThreads), smem, s,
+    hipLaunchKernelGGL((k_m2l_sym64<P, true>), dim3(unsigned(grid), unsigned(nsplit)), dim3(kSymThreads), smem, s,
                        0, 0, kp, mc, uint32_t(zero_cell * 3 * KC), ops, sl_off, orbits, row_std, dst, accumulate,
                        nsplit, pbuf, ad);
     hipError_t e = hipGetLastError();
@@ -602,25 +860,79 @@ hipError_t launch_m2l_sym64_adaptive(hipStream_t s, int p, int kp, const double 
                                    accumulate);
 }
 
-hipError_t launch_m2l_sym(hipStream_t s, int level, int periodic, int p, int kp, const float *mc, int64_t zero_cell,
-                          const float *ops, const int32_t *op_off, const int32_t *orbits, const int16_t *row_std,
-                          float *dst, int accumulate, float *part, size_t part_elems) {
-    if (!m2l_sym_supported(p) || level < 1) return hipErrorInvalidValue;
-    constexpr SymLayout SL = sym_layout(10);
+hipError_t launch_m2l_sym64_adaptive(hipStream_t s, int p, int kp, const double *mc, int64_t zero_cell,
+                                     const double *ops, const int32_t *sl_off, const int32_t *orbits,
+                                     const int16_t *row_std, double *dst, int accumulate, const SymAdapt &ad,
+                                     double *part, size_t part_elems) {
+    return with_degree(p, [&](auto pc) {
+        return m2l_sym64_adaptive<decltype(pc)::value>(s, kp, mc, zero_cell, ops, sl_off, orbits, row_std, dst,
+                                                       accumulate, ad, part, part_elems);
+    });
+}
+
+template <typename T>
+hipError_t launch_m2l_orbits(hipStream_t s, int lo, int hi, int periodic, int p, int kp, const T *mc,
+                             int64_t zero_cell, const T *ops, const int32_t *op_off, const int32_t *orbits,
+                             const int16_t *row_std, T *dst) {
+    if (!m2l_sym_supported(p) || lo < 1 || hi - lo > 6 || hi > kSymMaxSmall) return hipErrorInvalidValue;
+    OrbLevels lv;
+    lv.lo = lo;
+    lv.hi = hi;
+    int n = 0;
+    for (int l = lo; l <= hi; ++l) {
+        lv.tile0[l - lo] = n;
+        n += 8 * ((3 * (1 << (3 * (l - 1))) + 15) / 16);
+    }
+    // FP32 tables hold an offset per orbit, FP64 ones an offset per column slice
+    const bool f32 = sizeof(T) == 4;
+    auto go = [&](auto pc) {
+        constexpr int P = decltype(pc)::value;
+        constexpr SymLayout SL = sym_layout(P);
+        constexpr int RS = 2;
+        if ((uint64_t(zero_cell) + 1) * 48 * SL.nblk * sizeof(T) > (uint64_t(1) << 32)) return hipErrorInvalidValue;
+        hipLaunchKernelGGL((k_m2l_orbits<T, P, RS>), dim3(unsigned(n), RS), dim3(kOrbThreads), 0, s, lv, periodic, kp,
+                           mc, uint32_t(zero_cell * 48 * SL.nblk), ops, op_off, f32 ? 1 : SL.nblk,
+                           f32 ? kSymOrbits + 1 : kSymOrbits * SL.nblk + 1, orbits, row_std, dst);
+        return hipGetLastError();
+    };
+    return with_degree(p, go);
+}
+template hipError_t launch_m2l_orbits<float>(hipStream_t, int, int, int, int, int, const float *, int64_t,
+                                             const float *, const int32_t *, const int32_t *, const int16_t *,
+                                             float *);
+template hipError_t launch_m2l_orbits<double>(hipStream_t, int, int, int, int, int, const double *, int64_t,
+                                              const double *, const int32_t *, const int32_t *, const int16_t *,
+                                              double *);
+
+template <int P>
+hipError_t m2l_sym32(hipStream_t s, int level, int periodic, int kp, const float *mc, int64_t zero_cell,
+                     const float *ops, const int32_t *op_off, const int32_t *orbits, const int16_t *row_std,
+                     float *dst, int accumulate, float *part, size_t part_elems) {
+    if (level < 1) return hipErrorInvalidValue;
+    constexpr SymLayout SL = sym_layout(P);
     constexpr int KC = 16 * SL.nblk;
     // byte offsets into mc (the zero cell included) must fit 32 bits
     if ((uint64_t(zero_cell) + 1) * 3 * KC * sizeof(float) > (uint64_t(1) << 32)) return hipErrorInvalidValue;
     const int64_t ncell_t = int64_t(1) << (3 * (level - 1));
     const size_t smem = 2 * sizeof(float) * size_t(16 * SL.C * SL.nblk + 64);
-    int nsplit = part ? translate_splits(level, kSymTargets, kp, part_elems) : 1;
-    if (nsplit > kSymOrbits) nsplit = kSymOrbits;
+    const int tiles = int((ncell_t + kSymTargets - 1) / kSymTargets) * 8;
+    const int nsplit = part ? orbit_splits(tiles, size_t(ncell_t) * 8 * 3 * kp, part_elems) : 1;
     float *pbuf = nsplit > 1 ? part : nullptr;
-    const dim3 grid(unsigned((ncell_t + kSymTargets - 1) / kSymTargets * 8), unsigned(nsplit));
-    hipLaunchKernelGGL(k_m2l_sym<10>, grid, dim3(kSymThreads), smem, s, level, periodic, kp, mc,
+    const dim3 grid{unsigned(tiles), unsigned(nsplit)};
+    hipLaunchKernelGGL(k_m2l_sym<P>, grid, dim3(kSymThreads), smem, s, level, periodic, kp, mc,
                        uint32_t(zero_cell * 3 * KC), ops, op_off, orbits, row_std, dst, accumulate, nsplit, pbuf);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || nsplit == 1) return e;
     return launch_split_reduce(s, level, kp, SL.C, nsplit, pbuf, dst, accumulate);
+}
+
+hipError_t launch_m2l_sym(hipStream_t s, int level, int periodic, int p, int kp, const float *mc, int64_t zero_cell,
+                          const float *ops, const int32_t *op_off, const int32_t *orbits, const int16_t *row_std,
+                          float *dst, int accumulate, float *part, size_t part_elems) {
+    return with_degree(p, [&](auto pc) {
+        return m2l_sym32<decltype(pc)::value>(s, level, periodic, kp, mc, zero_cell, ops, op_off, orbits, row_std, dst,
+                                              accumulate, part, part_elems);
+    });
 }
 
 }  // namespace vmfmm

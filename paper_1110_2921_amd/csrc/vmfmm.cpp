@@ -548,6 +548,9 @@ vm_status ensure_sym_ops(vm_ctx *ctx, OpSet *set, int adjoint) {
         off[o * (kSymOrbits + 1) + kSymOrbits] = int32_t(ops.size());
         sl[o * (kSymOrbits * NB + 1) + kSymOrbits * NB] = int32_t(ops64.size());
     }
+    // the small-level kernel reads up to a block's rows past a short last block
+    ops.resize(ops.size() + 64, 0.0f);
+    ops64.resize(ops64.size() + 64, 0.0);
     OpSet::SymOps &so = set->sym[adjoint];
     VM_HIP(upload(so.ops, ops), "upload symmetric M2L");
     VM_HIP(upload(so.ops64, ops64), "upload symmetric M2L");
@@ -855,6 +858,40 @@ vm_status reinit_impl(vm_ctx *ctx, int64_t n, double *x, double *alpha, double s
     return VM_OK;
 }
 
+// M2L (adjoint 1: its transpose) of the levels lo .. hi by reflection orbits, from
+// the class-major multipoles mc of all levels (ncells cells, then the zero cell)
+// into the expansions `out` of all levels (rows < C overwritten).
+template <typename T>
+vm_status sym_m2l(vm_ctx *ctx, int lo, int hi, int periodic, int p, int kp, const T *mc, int64_t ncells, OpSet &ops,
+                  int adjoint, T *out) {
+    hipStream_t s = ctx->stream;
+    const OpSet::SymOps &so = ops.sym[adjoint];
+    const bool f32 = sizeof(T) == 4;
+    const T *op = f32 ? (const T *)so.ops.ptr : (const T *)so.ops64.ptr;
+    const int32_t *off = f32 ? so.off.as<int32_t>() : so.sl64.as<int32_t>();
+    const int32_t *orb = ops.sym_orb.as<int32_t>();
+    const int16_t *row = ops.sym_row.as<int16_t>();
+    const int kc = 16 * sym_layout(p).nblk;
+    const int small = std::min(hi, kSymMaxSmall);
+    Timed tm(ctx, VM_PH_M2L);
+    if (lo <= small)
+        VM_HIP(launch_m2l_orbits<T>(s, lo, small, periodic, p, kp, mc, ncells, op, off, orb, row, out), "M2L");
+    for (int l = std::max(lo, small + 1); l <= hi; ++l) {
+        const int64_t base = ((int64_t(1) << (3 * l)) - 1) / 7;
+        T *part = ctx->trpart.as<T>();
+        const size_t elems = ctx->trpart.bytes / sizeof(T);
+        if constexpr (sizeof(T) == 4)
+            VM_HIP(launch_m2l_sym(s, l, periodic, p, kp, mc + size_t(base) * 3 * kc, ncells - base, op, off, orb, row,
+                                  out + size_t(base) * 3 * kp, 0, part, elems),
+                   "M2L");
+        else
+            VM_HIP(launch_m2l_sym64(s, l, periodic, p, kp, mc + size_t(base) * 3 * kc, ncells - base, op, off, orb,
+                                    row, out + size_t(base) * 3 * kp, 0, part, elems),
+                   "M2L");
+    }
+    return VM_OK;
+}
+
 // One evaluation (the launch sequence of Sec. 3.1): tree, upward pass,
 // lattice, downward pass, then L2P and P2P at the particles (y == nullptr)
 // or at the m points y, which get a tree of their own (then no stretching).
@@ -873,10 +910,10 @@ vm_status fmm_impl(vm_ctx *ctx, int64_t n, const double *x, const double *alpha,
     if (vm_status st = ensure_ops(ctx, p, &ops); st != VM_OK) return st;
     if (opts->truncation == VM_TRIANGULAR)
         if (vm_status st = ensure_tri_ops(ctx, ops, 0); st != VM_OK) return st;
-    // square-truncation M2L by reflection orbits where its kernel is built (from
-    // level kSymMinLevel on; its source offsets are 32-bit byte offsets: levels
-    // up to 7 in FP32, 6 in FP64)
-    const bool use_sym = opts->truncation != VM_TRIANGULAR && m2l_sym_supported(p) && level >= kSymMinLevel &&
+    // square-truncation M2L by reflection orbits where its kernels are built (their
+    // source offsets are 32-bit byte offsets: levels up to 7 in FP32, 6 in FP64)
+    const int lmin = periodic ? 0 : 2, lm2l = periodic ? 1 : 2;   // coarsest levels with multipoles, with M2L
+    const bool use_sym = opts->truncation != VM_TRIANGULAR && m2l_sym_supported(p) && level >= lm2l &&
                          level <= (mixed ? 7 : 6);
     if (use_sym)
         if (vm_status st = ensure_sym_ops(ctx, ops, 0); st != VM_OK) return st;
@@ -938,7 +975,6 @@ vm_status fmm_impl(vm_ctx *ctx, int64_t n, const double *x, const double *alpha,
     }
 
     // --- near field (side stream) and far field (stream), then combine -------
-    const int lmin = periodic ? 0 : 2;
     const bool far = level >= lmin && !(periodic && K < 2 && level == 0);
     ctx->last_far = far;
     P2PArgs a;
@@ -1027,32 +1063,22 @@ vm_status fmm_impl(vm_ctx *ctx, int64_t n, const double *x, const double *alpha,
                 VM_HIP(launch_lattice<T>(s, p, kp, tlat, lev(M, 0), lev(L, 0)), "lattice");
                 have_parent = true;
             }
-            for (int l = periodic ? 1 : 2; l <= level; ++l) {
+            if (sym) {
+                // every level's M2L first (the multipoles are all there), the
+                // coarse ones in one launch; L2L then adds down the levels
+                if (vm_status st = sym_m2l<T>(ctx, lm2l, level, periodic, p, kp, mc, ncells, *ops, 0, L);
+                    st != VM_OK)
+                    return st;
+            }
+            for (int l = lm2l; l <= level; ++l) {
                 if (have_parent) {
                     Timed tm(ctx, VM_PH_L2L);
-                    VM_HIP(launch_translate<T>(s, 1, l, periodic, p, kp, l2l, lists, offs, lev(L, l - 1), lev(L, l), 0),
+                    VM_HIP(launch_translate<T>(s, 1, l, periodic, p, kp, l2l, lists, offs, lev(L, l - 1), lev(L, l),
+                                               sym ? 1 : 0),
                            "L2L");
                 }
-                Timed tm(ctx, VM_PH_M2L);
-                // the orbit kernel from level 4 on; the few cells of the coarser
-                // levels run the dense operators
-                if (sym && l >= kSymMinLevel) {
-                    const int64_t base = ((int64_t(1) << (3 * l)) - 1) / 7;
-                    if constexpr (sizeof(T) == 4)
-                        VM_HIP(launch_m2l_sym(s, l, periodic, p, kp, mc + size_t(base) * 3 * kc, ncells - base,
-                                              ops->sym[0].ops.as<float>(), ops->sym[0].off.as<int32_t>(),
-                                              ops->sym_orb.as<int32_t>(), ops->sym_row.as<int16_t>(), lev(L, l),
-                                              have_parent ? 1 : 0, ctx->trpart.as<float>(),
-                                              ctx->trpart.bytes / sizeof(float)),
-                               "M2L");
-                    else
-                        VM_HIP(launch_m2l_sym64(s, l, periodic, p, kp, mc + size_t(base) * 3 * kc, ncells - base,
-                                                ops->sym[0].ops64.as<double>(), ops->sym[0].sl64.as<int32_t>(),
-                                                ops->sym_orb.as<int32_t>(), ops->sym_row.as<int16_t>(), lev(L, l),
-                                                have_parent ? 1 : 0, ctx->trpart.as<double>(),
-                                                ctx->trpart.bytes / sizeof(double)),
-                               "M2L");
-                } else {
+                if (!sym) {
+                    Timed tm(ctx, VM_PH_M2L);
                     VM_HIP(launch_translate<T>(s, 0, l, periodic, p, kp, m2l, lists, offs, lev(M, l), lev(L, l),
                                                have_parent ? 1 : 0, ctx->trpart.as<T>(), ctx->trpart.bytes / sizeof(T),
                                                ctx->zeros.as<T>(), tri),
@@ -1664,7 +1690,8 @@ vm_status adjoint_impl(vm_ctx *ctx, int64_t n, const double *x, const double *al
     if (K >= 2)
         if (vm_status e = ensure_lattice_t(ctx, p, K, &tlat_t); e != VM_OK) return e;
     // the adjoint M2L by reflection orbits where the forward one runs so
-    const bool use_sym = opts->truncation != VM_TRIANGULAR && m2l_sym_supported(p) && level >= kSymMinLevel &&
+    const int lm2l = periodic ? 1 : 2;
+    const bool use_sym = opts->truncation != VM_TRIANGULAR && m2l_sym_supported(p) && level >= lm2l &&
                          level <= (mixed ? 7 : 6);
     const int64_t ncells = ((int64_t(1) << (3 * (level + 1))) - 1) / 7;
     if (use_sym) {
@@ -1727,33 +1754,19 @@ vm_status adjoint_impl(vm_ctx *ctx, int64_t n, const double *x, const double *al
             if (use_sym)
                 VM_HIP(launch_sym_pack<T>(s, ncells, kp, kc, Lb, ops->sym_mcsrc.as<int16_t>(), mc),
                        "M2L^T class-major local adjoints");
-            for (int l = periodic ? 1 : lmin; l <= level; ++l) {
+            if (use_sym)
+                if (vm_status e = sym_m2l<T>(ctx, lm2l, level, periodic, p, kp, mc, ncells, *ops, 1, Mb); e != VM_OK)
+                    return e;
+            for (int l = lm2l; l <= level; ++l) {
                 if (parent)
                     VM_HIP(launch_translate<T>(s, 1, l, periodic, p, kp, m2mT, lists, offs, lev(Mb, l - 1),
-                                               lev(Mb, l), 0),
+                                               lev(Mb, l), use_sym ? 1 : 0),
                            "M2M^T");
-                if (use_sym && l >= kSymMinLevel) {
-                    const int64_t base = ((int64_t(1) << (3 * l)) - 1) / 7;
-                    if constexpr (sizeof(T) == 4)
-                        VM_HIP(launch_m2l_sym(s, l, periodic, p, kp, mc + size_t(base) * 3 * kc, ncells - base,
-                                              ops->sym[1].ops.as<float>(), ops->sym[1].off.as<int32_t>(),
-                                              ops->sym_orb.as<int32_t>(), ops->sym_row.as<int16_t>(), lev(Mb, l),
-                                              parent ? 1 : 0, ctx->trpart.as<float>(),
-                                              ctx->trpart.bytes / sizeof(float)),
-                               "M2L^T");
-                    else
-                        VM_HIP(launch_m2l_sym64(s, l, periodic, p, kp, mc + size_t(base) * 3 * kc, ncells - base,
-                                                ops->sym[1].ops64.as<double>(), ops->sym[1].sl64.as<int32_t>(),
-                                                ops->sym_orb.as<int32_t>(), ops->sym_row.as<int16_t>(), lev(Mb, l),
-                                                parent ? 1 : 0, ctx->trpart.as<double>(),
-                                                ctx->trpart.bytes / sizeof(double)),
-                               "M2L^T");
-                } else {
+                if (!use_sym)
                     VM_HIP(launch_translate<T>(s, 0, l, periodic, p, kp, m2lT, lists, offs, lev(Lb, l), lev(Mb, l),
                                                parent ? 1 : 0, ctx->trpart.as<T>(), ctx->trpart.bytes / sizeof(T),
                                                ctx->zeros.as<T>(), tri),
                            "M2L^T");
-                }
                 parent = true;
             }
             VM_HIP(launch_p2m_adj<T>(s, int(nleaf), ni, parts, start, p, kp, inv_w, tab, ops->g_idx.as<int32_t>(), gw,
