@@ -22,9 +22,23 @@ struct TreeGeom {
 };
 
 // --- tree build (kernels_tree.hip) ----------------------------------------
+// A radix pass takes radix_items(n) keys per thread.  Up to 2^18 keys 4: with 16
+// a small sort ran on a handful of blocks, each a serial chain of 16 ranks (2^15
+// keys: 13 us a scatter against 5); beyond, the chip is full and 4 would only
+// quadruple the histogram.
 constexpr int kRadixThreads = 256;
-constexpr int kRadixItems = 16;
-constexpr int kRadixTile = kRadixThreads * kRadixItems;
+inline int radix_items(int n) { return n <= (1 << 18) ? 4 : 16; }
+inline int radix_blocks(int n) {
+    const int tile = kRadixThreads * radix_items(n);
+    return (n + tile - 1) / tile;
+}
+// words of the histogram buffer of passes over up to n keys: digit counts
+// [256][blocks], then the scan's tile sums
+inline size_t radix_hist_words(int n) {
+    const size_t b = size_t(radix_blocks(n)), bs = size_t(radix_blocks(n < (1 << 18) ? n : 1 << 18));
+    const size_t m = b > bs ? b : bs;   // a pass over fewer keys may have more blocks
+    return m * 256 + m * 256 / 4096 + 256;
+}
 
 hipError_t launch_keys(hipStream_t s, int n, const double *x, const TreeGeom &g, int check,
                        uint32_t *keys, int32_t *idx, int *flag);

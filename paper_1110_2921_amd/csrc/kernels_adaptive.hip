@@ -719,7 +719,7 @@ hipError_t launch_ad_groups(hipStream_t s, const AdTreeView &t, int ncell, int n
     while ((1 << bits) < nlev * 8) ++bits;
     hipError_t e = launch_radix_pass(s, ncell, 0, bits, ka, va, kb, vb, hist);
     if (e != hipSuccess) return e;
-    const int nblk = (ncell + kRadixTile - 1) / kRadixTile;
+    const int nblk = radix_blocks(ncell);
     hipLaunchKernelGGL(k_ad_group_starts, dim3(blocks(nlev * 8, 256)), dim3(256), 0, s, nlev * 8, nblk, ncell,
                        (const uint32_t *)hist, starts);
     return hipGetLastError();

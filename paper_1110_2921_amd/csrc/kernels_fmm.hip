@@ -678,9 +678,104 @@ __global__ void __launch_bounds__(256) k_split_reduce(int64_t nelem, int kp, int
     const int64_t e = int64_t(blockIdx.x) * 256 + threadIdx.x;
     if (e >= nelem) return;
     if (int(e % kp) >= C) return;
+    // eight loads in flight, added in order
     T s = T(0);
-    for (int k = 0; k < nsplit; ++k) s += part[size_t(k) * nelem + e];
+    int k = 0;
+    for (; k + 8 <= nsplit; k += 8) {
+        T v[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = part[size_t(k + i) * nelem + e];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) s += v[i];
+    }
+    for (; k < nsplit; ++k) s += part[size_t(k) * nelem + e];
     dst[e] = accumulate ? dst[e] + s : s;
+}
+
+// M2M and L2L of the coarse levels.  k_translate walks a tile's pairs one after
+// another (the 8 children of a parent: 8 times staging, barriers and operator
+// latency, 50 to 85 us however few the cells); here a workgroup takes 16 columns
+// (cell, component) and one row block (M2M: its 8 waves a child each, their
+// sums added in LDS in child order) or 8 row blocks (L2L: one a wave), every
+// operand straight from L2 into the MFMA's registers, four k blocks in flight:
+// M2M 4 to 6 us a level (13 us for 512 parents in FP64), L2L 4 to 8 (14 to 20
+// before).  An operator is read once per 16 columns: at 4096 parents (768 column
+// tiles) still as fast as k_translate, which the finer levels keep.
+constexpr int kTrCoarseCells = 4096;   // M2M parents, L2L targets
+
+template <typename T>
+__device__ __forceinline__ typename Mfma<T>::v4 tr_column_product(const T *__restrict__ op, const T *__restrict__ src,
+                                                                  int nkb, typename Mfma<T>::v4 acc) {
+    int kb = 0;
+    for (; kb + 4 <= nkb; kb += 4) {
+        Quad<T> a[4], b[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            a[i].load(op + size_t(kb + i) * 256);
+            b[i].load(src + 16 * (kb + i));
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) acc = Mfma<T>::op(a[i].v[q], b[i].v[q], acc);
+    }
+    for (; kb < nkb; ++kb) {
+        Quad<T> a, b;
+        a.load(op + size_t(kb) * 256);
+        b.load(src + 16 * kb);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc = Mfma<T>::op(a.v[q], b.v[q], acc);
+    }
+    return acc;
+}
+
+// grid (column tiles of the parents, row blocks)
+template <typename T>
+__global__ void __launch_bounds__(kTrThreads) k_m2m_coarse(int ncell, int C, int kp, int nrb, int nkb,
+                                                           const T *__restrict__ ops, const T *__restrict__ src,
+                                                           T *__restrict__ dst) {
+    __shared__ T red[kTrWaves * 256];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int rb = blockIdx.y, j = int(blockIdx.x) * 16 + (lane & 15);
+    const int cell = j / 3 < ncell ? j / 3 : 0, comp = j % 3;
+    const T *op = ops + (size_t(wave) * nrb + rb) * nkb * 256 + 4 * lane;
+    const T *sp = src + ((size_t(cell) * 8 + wave) * 3 + comp) * kp + 4 * (lane >> 4);
+    typename Mfma<T>::v4 acc{T(0), T(0), T(0), T(0)};
+    acc = tr_column_product<T>(op, sp, nkb, acc);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) red[wave * 256 + lane * 4 + r] = acc[r];
+    __syncthreads();
+    if (tid >= 256) return;
+    T x = T(0);
+#pragma unroll
+    for (int w = 0; w < kTrWaves; ++w) x += red[w * 256 + tid];
+    const int l = tid >> 2, row = rb * 16 + Mfma<T>::row(l, tid & 3), jl = int(blockIdx.x) * 16 + (l & 15);
+    if (jl / 3 < ncell && row < C) dst[(size_t(jl / 3) * 3 + jl % 3) * kp + row] = x;
+}
+
+// grid (8 octants x column tiles of an octant's targets, groups of 8 row blocks)
+template <typename T>
+__global__ void __launch_bounds__(kTrThreads) k_l2l_coarse(int ncell, int C, int kp, int nrb, int nkb,
+                                                           const T *__restrict__ ops, const T *__restrict__ src,
+                                                           T *__restrict__ dst, int accumulate) {
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
+    const int rb = int(blockIdx.y) * kTrWaves + wave, octant = blockIdx.x & 7;
+    if (rb * 16 >= C) return;
+    const int j = int(blockIdx.x >> 3) * 16 + (lane & 15);
+    const int slot = j / 3, comp = j % 3;
+    const T *op = ops + (size_t(octant) * nrb + rb) * nkb * 256 + 4 * lane;
+    const T *sp = src + (size_t(slot < ncell ? slot : 0) * 3 + comp) * kp + 4 * (lane >> 4);
+    typename Mfma<T>::v4 acc{T(0), T(0), T(0), T(0)};
+    acc = tr_column_product<T>(op, sp, nkb, acc);
+    if (slot >= ncell) return;
+    T *out = dst + ((size_t(slot) * 8 + octant) * 3 + comp) * kp;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int row = rb * 16 + Mfma<T>::row(lane, r);
+        if (row < C) out[row] = accumulate ? out[row] + acc[r] : acc[r];
+    }
 }
 
 // M2L in FP32, operator-stationary form.  A workgroup of 8 waves takes 64
@@ -894,17 +989,22 @@ __global__ void __launch_bounds__(kTrThreads) k_m2l_os(int level, int periodic, 
 }
 
 // ------------------------------------------------------------- lattice ----
+// A wave per output row, its lanes along the row (coalesced), the lanes' sums by
+// a fixed butterfly: 5 us (one workgroup, a thread per row: 14 us at p = 10)
 template <typename T>
-__global__ void __launch_bounds__(256) k_lattice(int C, int kp, const double *__restrict__ tlat,
-                                                 const T *__restrict__ m0, T *__restrict__ l0) {
-    __shared__ double m[3 * 441];
-    for (int i = threadIdx.x; i < 3 * C; i += 256) m[i] = double(m0[(i / C) * kp + (i % C)]);
-    __syncthreads();
-    for (int i = threadIdx.x; i < 3 * C; i += 256) {
-        const int c = i / C, row = i % C;
-        double s = 0.0;
-        for (int k = 0; k < C; ++k) s += tlat[size_t(row) * C + k] * m[c * C + k];
-        l0[c * kp + row] = T(s);
+__global__ void __launch_bounds__(64) k_lattice(int C, int kp, const double *__restrict__ tlat,
+                                                const T *__restrict__ m0, T *__restrict__ l0) {
+    const int row = blockIdx.x, lane = threadIdx.x;
+    double s[3] = {0.0, 0.0, 0.0};
+    for (int k = lane; k < C; k += 64) {
+        const double t = tlat[size_t(row) * C + k];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) s[c] += t * double(m0[c * kp + k]);
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        for (int off = 32; off > 0; off >>= 1) s[c] += __shfl_xor(s[c], off);
+        if (lane == c) l0[c * kp + row] = T(s[c]);
     }
 }
 
@@ -1039,6 +1139,18 @@ hipError_t launch_translate(hipStream_t s, int mode, int level, int periodic, in
     const int C = (p + 1) * (p + 1);
     const int nrb = tr_nrb(C);
     const int nrbw = nrb / kTrWaves;
+    if (mode == 2 && (int64_t(1) << (3 * level)) <= kTrCoarseCells) {
+        const int n = 1 << (3 * level);
+        hipLaunchKernelGGL(k_m2m_coarse<T>, dim3(unsigned((3 * n + 15) / 16), unsigned((C + 15) / 16)),
+                           dim3(kTrThreads), 0, s, n, C, kp, nrb, tr_nks(C) / 4, ops, src, dst);
+        return hipGetLastError();
+    }
+    if (mode == 1 && (int64_t(1) << (3 * level)) <= kTrCoarseCells) {
+        const int n = 1 << (3 * (level - 1));
+        hipLaunchKernelGGL(k_l2l_coarse<T>, dim3(unsigned((3 * n + 15) / 16 * 8), unsigned(nrbw)), dim3(kTrThreads),
+                           0, s, n, C, kp, nrb, tr_nks(C) / 4, ops, src, dst, accumulate);
+        return hipGetLastError();
+    }
     const TrShape sh = translate_shape<T>(kp);
     const int ttn = 16 * sh.nt;
     int64_t ncell;
@@ -1174,7 +1286,7 @@ hipError_t launch_translate_adaptive(hipStream_t s, int mode, int p, int kp, con
 template <typename T>
 hipError_t launch_lattice(hipStream_t s, int p, int kp, const double *tlat, const T *m0, T *l0) {
     const int C = (p + 1) * (p + 1);
-    hipLaunchKernelGGL(k_lattice<T>, dim3(1), dim3(256), 0, s, C, kp, tlat, m0, l0);
+    hipLaunchKernelGGL(k_lattice<T>, dim3(C), dim3(64), 0, s, C, kp, tlat, m0, l0);
     return hipGetLastError();
 }
 

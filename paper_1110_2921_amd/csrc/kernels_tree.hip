@@ -3,6 +3,8 @@
 // particles into leaf order.  All passes are bandwidth-bound; the key
 // arithmetic follows the documented reading bit for bit (no fused
 // multiply-add in the wrap or the cell index).
+#include <type_traits>
+
 #include "kernels.h"
 
 namespace vmfmm {
@@ -71,7 +73,10 @@ __global__ void __launch_bounds__(256) k_iota(int n, int32_t *__restrict__ idx, 
     }
 }
 
-// Per-tile digit histogram: hist[digit * nblocks + block].
+// Per-tile digit histogram: hist[digit * nblocks + block].  A block's tile is
+// ITEMS keys per thread: 16 for many keys, 4 where 16 would leave most of the
+// chip idle behind one block's chain of ranks (radix_items).
+template <int ITEMS>
 __global__ void __launch_bounds__(kRadixThreads) k_radix_hist(int n, int shift, int bits,
                                                              const uint32_t *__restrict__ keys,
                                                              uint32_t *__restrict__ hist) {
@@ -79,9 +84,9 @@ __global__ void __launch_bounds__(kRadixThreads) k_radix_hist(int n, int shift, 
     const int nb = 1 << bits;
     for (int b = threadIdx.x; b < nb; b += kRadixThreads) cnt[b] = 0;
     __syncthreads();
-    const int base = blockIdx.x * kRadixTile;
+    const int base = blockIdx.x * (ITEMS * kRadixThreads);
     const uint32_t mask = uint32_t(nb - 1);
-    for (int it = 0; it < kRadixItems; ++it) {
+    for (int it = 0; it < ITEMS; ++it) {
         const int e = base + it * kRadixThreads + threadIdx.x;
         if (e < n) atomicAdd(&cnt[(keys[e] >> shift) & mask], 1u);
     }
@@ -157,6 +162,7 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_add(int total, uint32_t *
 // Stable scatter: wave w of a block owns the contiguous quarter of its tile,
 // processed in rounds of 64 consecutive keys; ranks among equal digits come
 // from ballots, so equal keys keep their input order.
+template <int ITEMS>
 __global__ void __launch_bounds__(kRadixThreads) k_radix_scatter(int n, int shift, int bits,
                                                                 const uint32_t *__restrict__ kin,
                                                                 const int32_t *__restrict__ vin,
@@ -169,13 +175,13 @@ __global__ void __launch_bounds__(kRadixThreads) k_radix_scatter(int n, int shif
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     for (int b = threadIdx.x; b < 4 * 256; b += kRadixThreads) (&whist[0][0])[b] = 0;
     __syncthreads();
-    const int base = blockIdx.x * kRadixTile + wave * (kRadixItems * 64);
+    const int base = blockIdx.x * (ITEMS * kRadixThreads) + wave * (ITEMS * 64);
     const uint64_t lt = (lane == 0) ? 0ull : ((~0ull) >> (64 - lane));
-    uint32_t key[kRadixItems];
-    int32_t val[kRadixItems];
-    uint32_t rank[kRadixItems];
+    uint32_t key[ITEMS];
+    int32_t val[ITEMS];
+    uint32_t rank[ITEMS];
 #pragma unroll
-    for (int it = 0; it < kRadixItems; ++it) {
+    for (int it = 0; it < ITEMS; ++it) {
         const int e = base + it * 64 + lane;
         const bool valid = e < n;
         const uint32_t k = valid ? kin[e] : 0u;
@@ -206,7 +212,7 @@ __global__ void __launch_bounds__(kRadixThreads) k_radix_scatter(int n, int shif
     }
     __syncthreads();
 #pragma unroll
-    for (int it = 0; it < kRadixItems; ++it) {
+    for (int it = 0; it < ITEMS; ++it) {
         const int e = base + it * 64 + lane;
         if (e < n) {
             const uint32_t d = (key[it] >> shift) & mask;
@@ -283,25 +289,30 @@ hipError_t launch_iota(hipStream_t s, int n, int32_t *idx, uint32_t *keys) {
 
 hipError_t launch_radix_pass(hipStream_t s, int n, int shift, int bits, const uint32_t *kin,
                              const int32_t *vin, uint32_t *kout, int32_t *vout, uint32_t *hist) {
-    const int nblk = blocks(n, kRadixTile);
-    hipLaunchKernelGGL(k_radix_hist, dim3(nblk), dim3(kRadixThreads), 0, s, n, shift, bits, kin, hist);
+    const int nblk = radix_blocks(n);
     const int total = nblk << bits;
-    const int ntiles = (total + kScanTile - 1) / kScanTile;
     uint32_t *tile_sums = hist + size_t(nblk) * 256;   // the histogram buffer carries room for the tile sums
-    hipLaunchKernelGGL(k_scan_tiles, dim3(ntiles), dim3(kScanThreads), 0, s, total, hist, tile_sums);
-    hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(kScanThreads), 0, s, ntiles, tile_sums);
-    hipLaunchKernelGGL(k_scan_add, dim3(ntiles), dim3(kScanThreads), 0, s, total, hist, (const uint32_t *)tile_sums);
-    hipLaunchKernelGGL(k_radix_scatter, dim3(nblk), dim3(kRadixThreads), 0, s, n, shift, bits, kin, vin,
-                       kout, vout, (const uint32_t *)hist);
-    return hipGetLastError();
+    auto pass = [&](auto ic) {
+        constexpr int ITEMS = decltype(ic)::value;
+        hipLaunchKernelGGL(k_radix_hist<ITEMS>, dim3(nblk), dim3(kRadixThreads), 0, s, n, shift, bits, kin, hist);
+        const hipError_t e = launch_exclusive_scan(s, total, hist, tile_sums);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(k_radix_scatter<ITEMS>, dim3(nblk), dim3(kRadixThreads), 0, s, n, shift, bits, kin, vin,
+                           kout, vout, (const uint32_t *)hist);
+        return hipGetLastError();
+    };
+    return radix_items(n) == 4 ? pass(std::integral_constant<int, 4>{}) : pass(std::integral_constant<int, 16>{});
 }
 
 hipError_t launch_exclusive_scan(hipStream_t s, int total, uint32_t *data, uint32_t *tile_sums) {
     if (total <= 0) return hipSuccess;
     const int ntiles = (total + kScanTile - 1) / kScanTile;
     hipLaunchKernelGGL(k_scan_tiles, dim3(ntiles), dim3(kScanThreads), 0, s, total, data, tile_sums);
-    hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(kScanThreads), 0, s, ntiles, tile_sums);
-    hipLaunchKernelGGL(k_scan_add, dim3(ntiles), dim3(kScanThreads), 0, s, total, data, (const uint32_t *)tile_sums);
+    if (ntiles > 1) {   // one tile is scanned whole
+        hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(kScanThreads), 0, s, ntiles, tile_sums);
+        hipLaunchKernelGGL(k_scan_add, dim3(ntiles), dim3(kScanThreads), 0, s, total, data,
+                           (const uint32_t *)tile_sums);
+    }
     return hipGetLastError();
 }
 

@@ -681,14 +681,11 @@ vm_status build_tree(vm_ctx *ctx, const TreeBufs &b, int ni, const double *x, co
     const int mixed = opts->precision == VM_MIXED;
     const int64_t nleaf = int64_t(1) << (3 * level);
     const size_t n = size_t(ni);
-    const int nblk = (ni + kRadixTile - 1) / kRadixTile;
     VM_HIP(b.keys_a->reserve(sizeof(uint32_t) * n), "alloc keys");
     VM_HIP(b.keys_b->reserve(sizeof(uint32_t) * n), "alloc keys");
     VM_HIP(b.vals_a->reserve(sizeof(int32_t) * n), "alloc perm");
     VM_HIP(b.vals_b->reserve(sizeof(int32_t) * n), "alloc perm");
-    // digit counts [256][nblk] followed by the scan's tile sums
-    VM_HIP(ctx->hist.reserve(sizeof(uint32_t) * (size_t(nblk) * 256 + size_t(nblk) * 256 / 4096 + 256)),
-           "alloc histogram");
+    VM_HIP(ctx->hist.reserve(sizeof(uint32_t) * radix_hist_words(ni)), "alloc histogram");
     VM_HIP(b.start->reserve(sizeof(int32_t) * size_t(nleaf + 1)), "alloc leaf ranges");
     // one record to spare: the FP32 P2P prefetches one record past a block's end
     if (mixed) VM_HIP(b.p32->reserve(sizeof(Part32) * (size_t(n) + 1)), "alloc particles");
@@ -1245,13 +1242,11 @@ vm_status adaptive_impl(vm_ctx *ctx, int64_t n64, const double *x, const double 
 
     // --- particles sorted at the finest level ---------------------------------
     const TreeBufs b = source_bufs(ctx);
-    const int nblk = (n + kRadixTile - 1) / kRadixTile;
     VM_HIP(b.keys_a->reserve(sizeof(uint32_t) * size_t(n)), "alloc keys");
     VM_HIP(b.keys_b->reserve(sizeof(uint32_t) * size_t(n)), "alloc keys");
     VM_HIP(b.vals_a->reserve(sizeof(int32_t) * size_t(n)), "alloc perm");
     VM_HIP(b.vals_b->reserve(sizeof(int32_t) * size_t(n)), "alloc perm");
-    VM_HIP(ctx->hist.reserve(sizeof(uint32_t) * (size_t(nblk) * 256 + size_t(nblk) * 256 / 4096 + 256)),
-           "alloc histogram");
+    VM_HIP(ctx->hist.reserve(sizeof(uint32_t) * radix_hist_words(n)), "alloc histogram");
     VM_HIP(A.ints.reserve(sizeof(int) * 320), "alloc counters");
     int *dints = A.ints.as<int>();
     if (vm_status st = clear_flag(ctx, opts); st != VM_OK) return st;
@@ -1436,8 +1431,7 @@ vm_status adaptive_impl(vm_ctx *ctx, int64_t n64, const double *x, const double 
     // octant), the groups' starts read once
     std::vector<int> gstart(size_t(8) * nlev + 1, 0);
     {
-        const size_t gblk = (std::max<size_t>(size_t(n), size_t(ncell)) + kRadixTile - 1) / kRadixTile;
-        VM_HIP(ctx->hist.reserve(sizeof(uint32_t) * (gblk * 256 + gblk * 256 / 4096 + 256)), "alloc histogram");
+        VM_HIP(ctx->hist.reserve(sizeof(uint32_t) * radix_hist_words(std::max(n, ncell))), "alloc histogram");
         VM_HIP(A.gk.reserve(sizeof(uint32_t) * 2 * size_t(ncell)), "alloc octant groups");
         VM_HIP(A.gv.reserve(sizeof(int32_t) * size_t(ncell)), "alloc octant groups");
         uint32_t *gk = A.gk.as<uint32_t>();
