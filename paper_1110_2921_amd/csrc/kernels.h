@@ -89,7 +89,8 @@ hipError_t launch_p2m(hipStream_t s, int nleaf, const void *parts, const int32_t
 // dalpha in caller order, exactly as the P2P epilogue combines them; `far` is
 // then not written.
 struct NearCombine {
-    const double *near = nullptr;
+    const double *near = nullptr;    // [shares][15][n], the shares added in order
+    int shares = 1;
     const int32_t *perm = nullptr;   // caller index of each sorted target
     const double *alpha = nullptr;   // caller order [3][n] (stretching)
     double *u = nullptr, *dalpha = nullptr, *grad = nullptr;
@@ -161,8 +162,23 @@ struct P2PArgs {
     // non-null: the near field only, in sorted order, to near[15][n] (u, the
     // raw gradient sums, the strength sums q alpha; rows 3.. only with grad or
     // dalpha), combined with the far field afterwards by L2P (NearCombine)
+    // (shares > 1: the sources in `shares` parts, their sums to near[shares][15][n])
     double *near = nullptr;
+    int shares = 1;
+    const void *table = nullptr;     // the precision's pair table (pair_table64 / pair_table32), on the device
 };
+// Pair tables: Q(t) = g(sqrt t) / t^(3/2) as polynomials over segments of t,
+// 2^seg per octave from 2^kPairTabLo to 2^kPairTabHi and row 0 for [0,
+// 2^kPairTabLo).  FP64: four planes [rows][2] of coefficient pairs; FP32: a
+// plane [rows][4] and one [rows][4] with the fifth coefficient first.
+constexpr int kPairTabLo = -3, kPairTabHi = 11;
+constexpr int kPairSeg64 = 6, kPairCoefs64 = 8, kPairSeg32 = 5, kPairCoefs32 = 5;
+constexpr int pair_rows(int seg) { return ((kPairTabHi - kPairTabLo) << seg) + 1; }
+// uniform trees of at least so many leaves run a wave per leaf, smaller ones a
+// workgroup per leaf
+constexpr int kP2PSplitLeaves = 1 << 15;
+// shares a launch with a near buffer splits its sources into (see P2PArgs::near)
+int p2p_shares(int nleaf, int ntarget, bool mixed);
 hipError_t launch_p2p64(hipStream_t s, const P2PArgs &a, const Part64 *parts);
 hipError_t launch_p2p32(hipStream_t s, const P2PArgs &a, const Part32 *parts);
 

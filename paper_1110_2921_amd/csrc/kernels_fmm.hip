@@ -242,12 +242,16 @@ constexpr double kInv4PiL2P = 0.079577471545947667884441881686257181;
 // the far field uf, Jf: the P2P epilogue's operations in its order.
 __device__ __forceinline__ void combine_store(const NearCombine &c, size_t n, size_t gi, const double uf[3],
                                               const double Jf[9]) {
-    const double *nr = c.near;
+    auto near = [&](int row) {
+        double v = c.near[size_t(row) * n + gi];
+        for (int k = 1; k < c.shares; ++k) v += c.near[(size_t(k) * 15 + row) * n + gi];
+        return v;
+    };
     const int oi = c.perm[gi];
-    for (int b = 0; b < 3; ++b) c.u[b * n + oi] = nr[b * n + gi] * kInv4PiL2P + uf[b];
+    for (int b = 0; b < 3; ++b) c.u[b * n + oi] = near(b) * kInv4PiL2P + uf[b];
     if (!c.grad && !c.dalpha) return;
     double Sd[3];
-    for (int k = 0; k < 3; ++k) Sd[k] = nr[(12 + k) * n + gi];
+    for (int k = 0; k < 3; ++k) Sd[k] = near(12 + k);
     double al[3] = {0.0, 0.0, 0.0};
     if (c.dalpha)
         for (int k = 0; k < 3; ++k) al[k] = c.alpha[k * n + oi];
@@ -259,7 +263,7 @@ __device__ __forceinline__ void combine_store(const NearCombine &c, size_t n, si
             // antisymmetric part eps_rkm S_m of the near gradient J[r][k]
             const int m = 3 - r - k;
             const double anti = r == k ? 0.0 : ((k == (r + 1) % 3) ? Sd[m] : -Sd[m]);
-            const double J = (nr[(3 + 3 * r + k) * n + gi] + anti) * kInv4PiL2P + Jf[3 * r + k];
+            const double J = (near(3 + 3 * r + k) + anti) * kInv4PiL2P + Jf[3 * r + k];
             if (c.grad) c.grad[(3 * r + k) * n + oi] = J;
             if (c.scheme == 0) da[k] += al[r] * J;      // classic: sum_a alpha_a J[a][b]
             else da[r] += J * al[k];                     // transpose: sum_c J[b][c] alpha_c

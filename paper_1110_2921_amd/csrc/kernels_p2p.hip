@@ -1,20 +1,24 @@
 // Near field (P2P): exact regularised Biot-Savart velocity and gradient over
 // the 27 adjacent leaves (paper Sec. 3.1, last paragraph; kernel eqs. 5-8).
 //
-// One wave per target leaf, one target particle per lane.  Source particles
-// are read at wave-uniform addresses, so they arrive through scalar loads and
-// sit in SGPRs: every lane of the wave works on the same source at the same
-// time with no LDS traffic.  The pair kernel, with r = x_i - x_j and rho = r/sigma:
+// One target particle per lane.  Source particles are read at wave-uniform
+// addresses, so they arrive through scalar loads and sit in SGPRs: every lane of
+// the wave works on the same source at the same time.  The pair kernel, with
+// r = x_i - x_j and rho = r/sigma:
 //   q      = g(rho) / r^3,  g = erf(rho/sqrt2) - sqrt(2/pi) rho exp(-rho^2/2)
 //   q'/r   = (sqrt(2/pi) sigma^-3 exp(-rho^2/2) - 3 q) / r^2
 //   u     += q alpha_j x r
 //   J[a][b] += (q'/r) r_a (alpha_j x r)_b + q eps_abc alpha_j,c
 // For small rho both q and q'/r are even power series in rho (g is the
 // integral of the Gaussian mass, g' = sqrt(2/pi) rho^2 exp(-rho^2/2)).
-// A leaf's last target block of 32 or fewer particles is split over lane
-// groups that share out the sources.  The epilogue adds the far field
-// computed by L2P, contracts the gradient into the stretching term and
-// scatters to the caller's particle order.
+// A target block of 48 or fewer particles is split over lane groups that share
+// out the sources.  The sums go to the near buffer that L2P combines with the
+// far field, or, without one, through the epilogue here: far field, the
+// gradient's contraction into the stretching term, the caller's order.
+#include <algorithm>
+#include <type_traits>
+#include <utility>
+
 #include "kernels.h"
 
 namespace vmfmm {
@@ -380,52 +384,6 @@ __device__ __forceinline__ int xcd_leaf(int nleaf) {
     return (b & 7) * (nleaf >> 3) + (b >> 3);
 }
 
-__global__ void __launch_bounds__(64) k_p2p64(P2PArgs a, const Part64 *__restrict__ parts) {
-    const int leaf = xcd_leaf(a.nleaf), lane = threadIdx.x;
-    const int s0 = a.tstart[leaf], cnt = a.tstart[leaf + 1] - s0;
-    if (cnt == 0) return;
-    const Part64 *__restrict__ targets = static_cast<const Part64 *>(a.tparts);
-    LeafGeom L;
-    L.side = 1 << a.level;
-    L.cx = demorton(leaf, 0, a.level);
-    L.cy = demorton(leaf, 1, a.level);
-    L.cz = demorton(leaf, 2, a.level);
-    const Consts64 k = consts64(a.sigma);
-    const double zero[3] = {0.0, 0.0, 0.0};
-    // whole-wave blocks: one target per lane, wave-uniform sources
-    const int nfull = cnt - cnt % 64 + (cnt % 64 > 32 ? 64 : 0);
-    for (int base = 0; base < nfull; base += 64) {
-        const int rem = cnt - base;
-        const bool valid = lane < rem;
-        const Part64 me = targets[s0 + base + (valid ? lane : 0)];
-        double u[3] = {0, 0, 0}, Jr[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0}, S[3] = {0, 0, 0};
-        for (int nb = 0; nb < 27; ++nb) {
-            int js, je, dx, dy, dz;
-            if (!neighbour(a, L, nb, js, je, dx, dy, dz)) continue;
-            // x_i - x_j = (delta_i - d w) - delta_j, d = source - target cell offset
-            const double tx = me.dx - dx * a.w, ty = me.dy - dy * a.w, tz = me.dz - dz * a.w;
-            for (int j = js; j < je; ++j) acc64(parts[j], tx, ty, tz, k, u, Jr, S);
-        }
-        if (valid) epilogue(a, s0 + base + lane, true, u, zero, Jr, S, NoReduce{});
-    }
-    // a last block of rem <= 32 targets: lane groups share out the sources
-    const int rem = cnt - nfull;
-    if (rem <= 0) return;
-    const int E = pow2_ceil(rem);
-    const int t = lane & (E - 1), gi = lane / E, ng = 64 / E;
-    const bool valid = t < rem;
-    const Part64 me = targets[s0 + nfull + (valid ? t : 0)];
-    double u[3] = {0, 0, 0}, Jr[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0}, S[3] = {0, 0, 0};
-    for (int nb = 0; nb < 27; ++nb) {
-        int js, je, dx, dy, dz;
-        if (!neighbour(a, L, nb, js, je, dx, dy, dz)) continue;
-        const double tx = me.dx - dx * a.w, ty = me.dy - dy * a.w, tz = me.dz - dz * a.w;
-#pragma unroll 1
-        for (int j = js + gi; j < je; j += ng) acc64(parts[j], tx, ty, tz, k, u, Jr, S);
-    }
-    epilogue(a, s0 + nfull + t, valid && gi == 0, u, zero, Jr, S, GroupSum{E});
-}
-
 // Adaptive tree: one wave per target leaf (leaves in particle order, dealt to
 // the XCDs like the uniform leaves), sources from the leaf's P2P list: source
 // leaf b with image shift s contributes x_i - x_j - s L = (delta_i - D) -
@@ -492,121 +450,639 @@ __global__ void __launch_bounds__(64) k_p2p64_list(P2PArgs a, int nitem, const i
     epilogue(a, s0 + nfull + tt, valid && gi == 0, u, zero, Jr, S, GroupSum{E});
 }
 
-// Velocity sums: each block of at most kKahanBlock consecutive sources of a
-// leaf is summed plainly in FP32 (up), and the block sums enter the running
-// total through Kahan's compensated addition (us, uc).  Per pair that is one
-// FMA per component instead of a compensated step (4 instructions), and the
-// rounding left is that of 16-term FP32 sums, around 1e-7 of the block's terms.
-constexpr int kKahanBlock = 16;
+// --- uniform tree ------------------------------------------------------------
+// Workgroups of 8 waves (the pair table in LDS is shared), one target per lane,
+// sources at wave-uniform addresses (scalar loads).  Two ways to deal out the
+// work:
+//   SPLIT   a workgroup takes one leaf at a time: the sources of its 27
+//           neighbour leaves, concatenated, go to the waves in equal contiguous
+//           shares, every wave holds the same targets, and the waves' sums are
+//           added through LDS in wave order.  A tree of few leaves needs this:
+//           with one wave per leaf, 64 leaves ran 64 waves on 1024 SIMDs, each
+//           through 1728 sources in turn (16^3 FP64: 602 us; split 30 us).
+//           Trees of fewer leaves than the chip holds workgroups also deal a
+//           leaf's target blocks over gridDim.y and its sources over gridDim.z
+//           (partial near fields, added by L2P).
+//   !SPLIT  a wave per leaf, without the reduction, from kP2PSplitLeaves on, where
+//           the leaves fill the chip many times over (128^3, one evaluation:
+//           FP64 13.7 against 14.5 ms split, a mixed Heun step 14.6 against 15.9).
+// Workgroups go to the 8 XCDs round-robin, so workgroup b takes leaves of the
+// (b mod 8)-th eighth of the Morton order, whose neighbour leaves that XCD's L2
+// then shares.
+constexpr int kP2PWaves = 8;
+constexpr int kP2PThreads = 64 * kP2PWaves;
+constexpr int kNearRows = 15;     // u, gradient sums, strength sums
+constexpr int kRedRows = 3;       // values per reduction round
+constexpr int kRedDoubles = kRedRows * kP2PThreads + kNearRows * 64;
 
-struct Acc32 {
-    float us[3], uc[3], up[3], Jr[9], S[3];
-};
+// lane group size of a target piece of `rem` targets: 64 (a whole wave) or the
+// lane groups' power of two; a remainder a little over a power of two is cut
+// there, the rest is a piece of its own (34 targets: 32 + 2, 34 / 64 of a
+// whole-wave pass instead of all of it)
+__device__ __forceinline__ int piece_lanes(int rem) {
+    if (rem > 48) return 64;
+    const int e = pow2_ceil(rem);
+    return e > 8 && 4 * rem <= 3 * e ? e >> 1 : e;
+}
 
-__device__ __forceinline__ void kahan_flush(Acc32 &A) {
+template <int K>
+using IC = std::integral_constant<int, K>;
+
+template <class F, int... K>
+__device__ __forceinline__ void for_rows(F &&f, std::integer_sequence<int, K...>) {
+    (f(IC<K>{}), ...);
+}
+
+// u, J and dalpha/dt of sorted target gi from its near sums f(row), with the
+// far field where there is one, in caller order
+template <class F>
+__device__ __forceinline__ void finish(const P2PArgs &a, int gi, bool write, F f) {
+    if (!write) return;
+    const size_t n = size_t(a.n);
+    const int oi = a.perm[gi];
+    for (int b = 0; b < 3; ++b) a.u[b * n + oi] = f(b) * kInv4Pi + (a.have_far ? a.far[b * n + gi] : 0.0);
+    if (!a.grad && !a.dalpha) return;
+    double al[3] = {0.0, 0.0, 0.0};
+    if (a.dalpha)
+        for (int c = 0; c < 3; ++c) al[c] = a.alpha[c * n + oi];
+    double da[3] = {0.0, 0.0, 0.0};
 #pragma unroll
-    for (int b = 0; b < 3; ++b) {
-        const float y = A.up[b] - A.uc[b];
-        const float t = A.us[b] + y;
-        A.uc[b] = (t - A.us[b]) - y;
-        A.us[b] = t;
-        A.up[b] = 0.0f;
+    for (int r = 0; r < 3; ++r) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            // antisymmetric part eps_abc S_c of the near gradient J[r][c]
+            const int k = 3 - r - c;
+            const double anti = r == c ? 0.0 : ((c == (r + 1) % 3) ? f(12 + k) : -f(12 + k));
+            double J = (f(3 + 3 * r + c) + anti) * kInv4Pi;
+            if (a.have_far) J += a.far[(3 + 3 * r + c) * n + gi];
+            if (a.grad) a.grad[(3 * r + c) * n + oi] = J;
+            if (a.scheme == 0) da[c] += al[r] * J;      // classic: sum_a alpha_a J[a][b]
+            else da[r] += J * al[c];                     // transpose: sum_c J[b][c] alpha_c
+        }
     }
+    if (a.dalpha)
+        for (int b = 0; b < 3; ++b) a.dalpha[b * n + oi] = da[b];
 }
 
-__device__ __forceinline__ void acc32(const Part32 &s, float tx, float ty, float tz, const Consts32 &k, Acc32 &A) {
-    const float rx = tx - s.dx, ry = ty - s.dy, rz = tz - s.dz;
-    const float r2 = rx * rx + ry * ry + rz * rz;
-    float q, dq;
-    pair32(r2, k, q, dq);
-    const float c[3] = {s.ay * rz - s.az * ry, s.az * rx - s.ax * rz, s.ax * ry - s.ay * rx};
+template <class POL, bool SPLIT>
+__device__ __forceinline__ void p2p_leaves(const P2PArgs &a, const typename POL::Rec *__restrict__ parts,
+                                           const POL &pol, double *red) {
+    using Rec = typename POL::Rec;
+    using T = typename POL::Real;
+    double *fin = red + kRedRows * kP2PThreads;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const Rec *__restrict__ targets = static_cast<const Rec *>(a.tparts);
+    const size_t n = size_t(a.n);
+    const int run = a.nleaf / int(gridDim.x);   // leaves of this workgroup
+    const bool xcd = a.nleaf % 8 == 0 && gridDim.x % 8 == 0;
+    const int first = xcd ? int(blockIdx.x & 7) * (a.nleaf >> 3) + int(blockIdx.x >> 3) * run : int(blockIdx.x) * run;
+    const int nsh = int(gridDim.z) * kP2PWaves, sh = int(blockIdx.z) * kP2PWaves + wave;
+    const T w = T(a.w);
+    for (int li = SPLIT ? 0 : wave; li < run; li += SPLIT ? 1 : kP2PWaves) {
+        const int leaf = first + li;
+        const int s0 = a.tstart[leaf], cnt = a.tstart[leaf + 1] - s0;
+        if (cnt == 0) continue;
+        // lane nb < 27: the neighbour's first source and the end of its sources in
+        // the concatenated list
+        int nb_js = 0, nb_end = 0;
+        {
+            LeafGeom L;
+            L.side = 1 << a.level;
+            L.cx = demorton(leaf, 0, a.level);
+            L.cy = demorton(leaf, 1, a.level);
+            L.cz = demorton(leaf, 2, a.level);
+            int je = 0, dx, dy, dz;
+            if (lane < 27 && !neighbour(a, L, lane, nb_js, je, dx, dy, dz)) nb_js = je = 0;
+            nb_end = je - nb_js;
 #pragma unroll
-    for (int b = 0; b < 3; ++b) A.up[b] = fmaf(q, c[b], A.up[b]);
-    A.S[0] += q * s.ax;
-    A.S[1] += q * s.ay;
-    A.S[2] += q * s.az;
-    const float t0 = dq * c[0], t1 = dq * c[1], t2 = dq * c[2];
-    A.Jr[0] += rx * t0; A.Jr[1] += rx * t1; A.Jr[2] += rx * t2;
-    A.Jr[3] += ry * t0; A.Jr[4] += ry * t1; A.Jr[5] += ry * t2;
-    A.Jr[6] += rz * t0; A.Jr[7] += rz * t1; A.Jr[8] += rz * t2;
-}
-
-// Mixed precision: FP32 pair arithmetic, Kahan-compensated velocity sums.
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8, 8))) k_p2p32(P2PArgs a, const Part32 *__restrict__ parts) {
-    const int leaf = xcd_leaf(a.nleaf), lane = threadIdx.x;
-    const int s0 = a.tstart[leaf], cnt = a.tstart[leaf + 1] - s0;
-    if (cnt == 0) return;
-    const Part32 *__restrict__ targets = static_cast<const Part32 *>(a.tparts);
-    LeafGeom L;
-    L.side = 1 << a.level;
-    L.cx = demorton(leaf, 0, a.level);
-    L.cy = demorton(leaf, 1, a.level);
-    L.cz = demorton(leaf, 2, a.level);
-    const Consts32 k = consts32(a.sigma);
-    const float w = float(a.w);
-    // whole-wave blocks: one target per lane, wave-uniform sources
-    const int nfull = cnt - cnt % 64 + (cnt % 64 > 32 ? 64 : 0);
-    for (int base = 0; base < nfull; base += 64) {
-        const int rem = cnt - base;
-        const bool valid = lane < rem;
-        const Part32 me = targets[s0 + base + (valid ? lane : 0)];
-        Acc32 A;
-        for (int c = 0; c < 3; ++c) A.us[c] = A.uc[c] = A.up[c] = A.S[c] = 0.0f;
-        for (int c = 0; c < 9; ++c) A.Jr[c] = 0.0f;
-        for (int nb = 0; nb < 27; ++nb) {
-            int js, je, dx, dy, dz;
-            if (!neighbour(a, L, nb, js, je, dx, dy, dz) || js >= je) continue;
-            const float tx = me.dx - float(dx) * w, ty = me.dy - float(dy) * w, tz = me.dz - float(dz) * w;
-            // the next record is fetched (scalar load) while the current one is
-            // evaluated, across the leaf's blocks; past the leaf's end that is the
-            // following record, which exists (the records are allocated with one
-            // to spare) and is unused
-            const Part32 *__restrict__ ps = parts + js;
-            Part32 cur = ps[0];
-            for (int jb = js; jb < je; jb += kKahanBlock) {
-                const int jend = min(jb + kKahanBlock, je);
-#pragma unroll 2
-                for (int j = jb; j < jend; ++j) {
-                    const Part32 nxt = ps[1];
-                    ++ps;
-                    acc32(cur, tx, ty, tz, k, A);
-                    cur = nxt;
-                }
-                kahan_flush(A);
+            for (int d = 1; d < 32; d <<= 1) {
+                const int y = __shfl_up(nb_end, d, 64);
+                if (lane >= d) nb_end += y;
             }
         }
-        if (valid) epilogue(a, s0 + base + lane, true, A.us, A.uc, A.Jr, A.S, NoReduce{});
-    }
-    // a last block of rem <= 32 targets: lane groups share out the sources, their
-    // partial sums are combined in FP64
-    const int rem = cnt - nfull;
-    if (rem <= 0) return;
-    const int E = pow2_ceil(rem);
-    const int t = lane & (E - 1), gi = lane / E, ng = 64 / E;
-    const bool valid = t < rem;
-    const Part32 me = targets[s0 + nfull + (valid ? t : 0)];
-    Acc32 A;
-    for (int c = 0; c < 3; ++c) A.us[c] = A.uc[c] = A.up[c] = A.S[c] = 0.0f;
-    for (int c = 0; c < 9; ++c) A.Jr[c] = 0.0f;
-    for (int nb = 0; nb < 27; ++nb) {
-        int js, je, dx, dy, dz;
-        if (!neighbour(a, L, nb, js, je, dx, dy, dz)) continue;
-        const float tx = me.dx - float(dx) * w, ty = me.dy - float(dy) * w, tz = me.dz - float(dz) * w;
-        // this lane group takes every ng-th source: blocks of kKahanBlock of its own sources
-        for (int jb = js + gi; jb < je; jb += ng * kKahanBlock) {
-            const int jend = min(jb + ng * kKahanBlock, je);
-#pragma unroll 1
-            for (int j = jb; j < jend; j += ng) acc32(parts[j], tx, ty, tz, k, A);
-            kahan_flush(A);
+        const int64_t total = __builtin_amdgcn_readlane(nb_end, 26);
+        const int q0 = SPLIT ? int(total * sh / nsh) : 0, q1 = SPLIT ? int(total * (sh + 1) / nsh) : int(total);
+        int piece = 0;
+        for (int base = 0; base < cnt; ++piece) {
+            const int E = piece_lanes(cnt - base);
+            const int b0 = base;
+            base += E;
+            if (SPLIT && piece % int(gridDim.y) != int(blockIdx.y)) continue;
+            const int t = lane & (E - 1), grp = lane / E, ng = 64 / E;
+            const bool write = b0 + t < cnt && grp == 0;
+            const int gi = s0 + (b0 + t < cnt ? b0 + t : b0);
+            const Rec me = targets[gi];
+            typename POL::Acc A;
+            POL::clear(A);
+            int c1 = 0;
+            for (int nb = 0; nb < 27; ++nb) {
+                const int c0 = c1;
+                c1 = __builtin_amdgcn_readlane(nb_end, nb);
+                const int p0 = q0 > c0 ? q0 : c0, p1 = q1 < c1 ? q1 : c1;
+                if (p0 >= p1) continue;
+                const int js = __builtin_amdgcn_readlane(nb_js, nb) + (p0 - c0), je = js + (p1 - p0);
+                // x_i - x_j = (delta_i - d w) - delta_j, d = source - target cell offset
+                const int dx = nb % 3 - 1, dy = (nb / 3) % 3 - 1, dz = nb / 9 - 1;
+                const T tx = me.dx - T(dx) * w, ty = me.dy - T(dy) * w, tz = me.dz - T(dz) * w;
+                if (E == 64) pol.uniform(parts, js, je, tx, ty, tz, A);
+                else pol.grouped(parts, js + grp, je, ng, tx, ty, tz, A);
+            }
+            // the lane groups' sums (fixed butterfly)
+            auto sum = [&](auto kc) {
+                double x = pol.template value<decltype(kc)::value>(A);
+                for (int off = E; off < 64; off <<= 1) x += __shfl_xor(x, off);
+                return x;
+            };
+            const bool all = a.grad || a.dalpha;
+            if constexpr (!SPLIT) {
+                if (a.near) {
+                    auto put = [&](auto kc) {
+                        const double x = sum(kc);
+                        if (write) a.near[size_t(decltype(kc)::value) * n + gi] = x;
+                    };
+                    for_rows(put, std::make_integer_sequence<int, 3>{});
+                    if (all)
+                        for_rows([&](auto kc) { put(IC<decltype(kc)::value + 3>{}); },
+                                 std::make_integer_sequence<int, kNearRows - 3>{});
+                } else {
+                    double f[kNearRows];
+                    for_rows([&](auto kc) { f[decltype(kc)::value] = sum(kc); },
+                             std::make_integer_sequence<int, kNearRows>{});
+                    finish(a, gi, write, [&](int r) { return f[r]; });
+                }
+            } else {
+                // then the waves', kRedRows values a round
+                auto round = [&](auto rc) {
+                    constexpr int r0 = decltype(rc)::value * kRedRows;
+                    for_rows([&](auto kc) {
+                        constexpr int k = decltype(kc)::value;
+                        red[(k * kP2PWaves + wave) * 64 + lane] = sum(IC<r0 + k>{});
+                    }, std::make_integer_sequence<int, kRedRows>{});
+                    __syncthreads();
+                    if (tid < 64 * kRedRows) {
+                        const int k = tid >> 6;
+                        double x = 0.0;
+#pragma unroll
+                        for (int q = 0; q < kP2PWaves; ++q) x += red[(k * kP2PWaves + q) * 64 + lane];
+                        if (!a.near) fin[(r0 + k) * 64 + lane] = x;
+                        else if (write) a.near[(size_t(blockIdx.z) * kNearRows + r0 + k) * n + gi] = x;
+                    }
+                    __syncthreads();
+                };
+                round(IC<0>{});
+                if (all)
+                    for_rows([&](auto kc) { round(IC<decltype(kc)::value + 1>{}); },
+                             std::make_integer_sequence<int, kNearRows / kRedRows - 1>{});
+                if (!a.near && wave == 0) finish(a, gi, write, [&](int r) { return fin[64 * r + lane]; });
+            }
         }
     }
-    epilogue(a, s0 + nfull + t, valid && gi == 0, A.us, A.uc, A.Jr, A.S, GroupSum{E});
 }
+
+// The pair function from a table.  With t = rho^2 = r^2 / sigma^2,
+//   q = Q(t) / sigma^3,  q'/r = 2 Q'(t) / sigma^5,  Q(t) = g / rho^3:
+// both are one smooth function of t and its derivative, so one polynomial
+// serves both (Horner with the derivative alongside), without a reciprocal
+// square root, an exponential or erfc per pair.  Rows are segments of t, 2^SEG
+// per octave from 2^kPairTabLo to 2^kPairTabHi (index: the exponent and the top
+// mantissa bits of t) and row 0 for [0, 2^kPairTabLo); a row holds the
+// coefficients of Q in x = t - c, c the segment's centre, chosen so that 2 Q'
+// is the truncated Chebyshev series of q'/r (host, extended precision).  From
+// t = 2^kPairTabHi on g is 1 and Q = t^-3/2: t is scaled by 4^-e into the last
+// two octaves and the results by 8^-e and 32^-e.
+// FP64: 64 segments per octave, degree 7, largest relative error against
+// 40-digit arithmetic 2.1e-16 in q and 7.0e-16 in q'/r (the polynomial erfc and
+// exponential of pair64: 3.2e-15 and 2.9e-14); FP32: 32 per octave, degree 4,
+// 1.0e-7 and 1.6e-7 (pair32: 5.9e-7 and 3.5e-6).
+// The table (FP64 57 KB, FP32 9 KB) sits in LDS in planes of 16 bytes per row,
+// so that the lanes' rows spread over the banks (a 16-byte gather of 64 lanes
+// takes 14 cycles, 4 of them without conflicts).
+// FP64: 50 instead of 97 FP64 instructions a pair at 4 instead of 2 waves per
+// SIMD, 8.0 instead of 13.3 ms at 128^3 (350 cycles a wave and source, of which
+// VALU 215 and LDS 221 of the CU's); FP32: 25.9 against 26.2 ms at 256^3, LDS
+// gathers for what the two transcendentals took.
+typedef double dbl2 __attribute__((ext_vector_type(2)));
+typedef float flt4 __attribute__((ext_vector_type(4)));
+
+typedef const __attribute__((address_space(3))) char *LdsBytes;
+
+template <typename T> struct PairTab;
+template <> struct PairTab<double> {
+    static constexpr int seg = kPairSeg64, rows = pair_rows(kPairSeg64);
+    static constexpr int bytes = rows * 8 * kPairCoefs64;
+    static constexpr int mant = 20, bias = 1023;   // of the high word
+    static __device__ __forceinline__ int word(double t) { return __double2hiint(t); }
+    static __device__ __forceinline__ double real(int w) { return __hiloint2double(w, 0); }
+    static __device__ __forceinline__ double with(double t, int w) { return __hiloint2double(w, __double2loint(t)); }
+    struct Row {
+        dbl2 c01, c23, c45, c67;
+    };
+    static __device__ __forceinline__ Row load(LdsBytes row) {
+        typedef const __attribute__((address_space(3))) dbl2 *P;
+        const P c = (P)row;
+        return {c[0], c[rows], c[2 * rows], c[3 * rows]};
+    }
+    static __device__ __forceinline__ void eval(const Row &r, double x, double &Q, double &H) {
+        const dbl2 c01 = r.c01, c23 = r.c23, c45 = r.c45, c67 = r.c67;
+        double d = c67.y, p = fma(c67.y, x, c67.x);
+        d = fma(d, x, p); p = fma(p, x, c45.y);
+        d = fma(d, x, p); p = fma(p, x, c45.x);
+        d = fma(d, x, p); p = fma(p, x, c23.y);
+        d = fma(d, x, p); p = fma(p, x, c23.x);
+        d = fma(d, x, p); p = fma(p, x, c01.y);
+        Q = fma(p, x, c01.x);
+        H = fma(d, x, p);
+    }
+    static __device__ __forceinline__ double scale(double v, int e) { return ldexp(v, e); }
+};
+template <> struct PairTab<float> {
+    static constexpr int seg = kPairSeg32, rows = pair_rows(kPairSeg32);
+    static constexpr int bytes = rows * 16 * 2;
+    static constexpr int mant = 23, bias = 127;
+    static __device__ __forceinline__ int word(float t) { return __float_as_int(t); }
+    static __device__ __forceinline__ float real(int w) { return __int_as_float(w); }
+    static __device__ __forceinline__ float with(float, int w) { return __int_as_float(w); }
+    struct Row {
+        flt4 c0;
+        float c4;
+    };
+    static __device__ __forceinline__ Row load(LdsBytes row) {
+        typedef const __attribute__((address_space(3))) flt4 *P;
+        const P c = (P)row;
+        return {c[0], ((const __attribute__((address_space(3))) float *)(c + rows))[0]};
+    }
+    static __device__ __forceinline__ void eval(const Row &r, float x, float &Q, float &H) {
+        const flt4 c0 = r.c0;
+        const float c4 = r.c4;
+        float d = c4, p = fmaf(c4, x, c0.w);
+        d = fmaf(d, x, p); p = fmaf(p, x, c0.z);
+        d = fmaf(d, x, p); p = fmaf(p, x, c0.y);
+        Q = fmaf(p, x, c0.x);
+        H = fmaf(d, x, p);
+    }
+    static __device__ __forceinline__ float scale(float v, int e) { return ldexpf(v, e); }
+};
+
+// exponent e that brings t below the table's end (0 within the table)
+template <typename T>
+__device__ __forceinline__ int table_shift(T t) {
+    using P = PairTab<T>;
+    const int w = P::word(t);
+    return w >= ((P::bias + kPairTabHi) << P::mant) ? ((w >> P::mant) - (P::bias + kPairTabHi - 2)) >> 1 : 0;
+}
+
+// t's row, and x = t - c
+template <typename T>
+__device__ __forceinline__ LdsBytes table_row(T t, uint32_t tab, T &x) {
+    using P = PairTab<T>;
+    constexpr int sh = P::mant - P::seg;
+    constexpr int lo = ((P::bias + kPairTabLo) << P::seg) - 1, hi = lo + P::rows - 1;
+    int idx = P::word(t) >> sh;
+    idx = idx < lo ? lo : (idx > hi ? hi : idx);
+    x = t - P::real((idx << sh) | (1 << (sh - 1)));
+    // one LDS address (the table's, less its first row's index, in `tab`), the
+    // planes at immediate offsets from it
+    uint32_t at = (uint32_t(idx) << 4) + tab;
+    asm("" : "+v"(at));
+    return (LdsBytes)at;
+}
+// what table_row takes for a table at LDS address `at`
+template <typename T>
+__device__ __forceinline__ uint32_t table_base(uint32_t at) {
+    using P = PairTab<T>;
+    return at - 16u * uint32_t(((P::bias + kPairTabLo) << P::seg) - 1);
+}
+
+// Q and Q' (H) of NS pairs at squared distances r2
+template <int NS, typename T>
+__device__ __forceinline__ void table_pairs(const T (&r2)[NS], T inv_s2, uint32_t tab, T (&q)[NS], T (&h)[NS]) {
+    using P = PairTab<T>;
+    T t[NS];
+    int w = 0;
+#pragma unroll
+    for (int i = 0; i < NS; ++i) {
+        t[i] = r2[i] * inv_s2;
+        w = max(w, P::word(t[i]));
+    }
+    // beyond the table (wave-uniform test, rare): t scaled down before, the results after
+    const bool beyond = __builtin_amdgcn_ballot_w64(w >= ((P::bias + kPairTabHi) << P::mant)) != 0;
+    if (__builtin_expect(beyond, 0)) {
+#pragma unroll
+        for (int i = 0; i < NS; ++i) t[i] = P::with(t[i], P::word(t[i]) - (table_shift(t[i]) << (P::mant + 1)));
+    }
+    // every row's reads issued before the first polynomial
+    typename P::Row row[NS];
+#pragma unroll
+    for (int i = 0; i < NS; ++i) row[i] = P::load(table_row(t[i], tab, t[i]));
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < NS; ++i) P::eval(row[i], t[i], q[i], h[i]);
+    if (__builtin_expect(beyond, 0)) {
+#pragma unroll
+        for (int i = 0; i < NS; ++i) {
+            const int e = table_shift(r2[i] * inv_s2);
+            q[i] = P::scale(q[i], -3 * e);
+            h[i] = P::scale(h[i], -5 * e);
+        }
+    }
+}
+
+// One precision's pair arithmetic.  TAB: the pair function from the table, in
+// units of sigma (the sums are scaled by cu = 1/sigma^3 and cj = 2/sigma^5 at the
+// end); else pair64 / pair32, the form for cores so small beside the leaf that
+// those units would leave the type's range (launch_p2p*).
+template <bool TAB>
+struct Pol64 {
+    using Rec = Part64;
+    using Real = double;
+    uint32_t tab;
+    double inv_s2, cu, cj;
+    Consts64 k;
+    struct Acc {
+        double u[3], J[9], S[3];
+    };
+    static __device__ __forceinline__ void clear(Acc &A) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) A.u[c] = A.S[c] = 0.0;
+#pragma unroll
+        for (int c = 0; c < 9; ++c) A.J[c] = 0.0;
+    }
+    __device__ __forceinline__ Pol64(double sigma, uint32_t table) : tab(table), inv_s2(0.0), cu(1.0), cj(1.0) {
+        if constexpr (TAB) {
+            const double is = 1.0 / sigma;
+            inv_s2 = is * is;
+            cu = is * is * is;
+            cj = 2.0 * cu * inv_s2;
+        } else {
+            k = consts64(sigma);
+        }
+    }
+    __device__ __forceinline__ void add(const Part64 &s, const double (&r)[3], double q, double h, Acc &A) const {
+        const double c0 = s.ay * r[2] - s.az * r[1];
+        const double c1 = s.az * r[0] - s.ax * r[2];
+        const double c2 = s.ax * r[1] - s.ay * r[0];
+        A.u[0] += q * c0;
+        A.u[1] += q * c1;
+        A.u[2] += q * c2;
+        A.S[0] += q * s.ax;
+        A.S[1] += q * s.ay;
+        A.S[2] += q * s.az;
+        const double t0 = h * c0, t1 = h * c1, t2 = h * c2;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            A.J[3 * i] += r[i] * t0;
+            A.J[3 * i + 1] += r[i] * t1;
+            A.J[3 * i + 2] += r[i] * t2;
+        }
+    }
+    // NS sources at once (one test for pairs beyond the table)
+    template <int NS>
+    __device__ __forceinline__ void pairs(const Part64 *__restrict__ src, double tx, double ty, double tz,
+                                          Acc &A) const {
+        Part64 s[NS];
+        double r[NS][3], r2[NS], q[NS], h[NS];
+#pragma unroll
+        for (int i = 0; i < NS; ++i) {
+            s[i] = src[i];
+            r[i][0] = tx - s[i].dx;
+            r[i][1] = ty - s[i].dy;
+            r[i][2] = tz - s[i].dz;
+            r2[i] = r[i][0] * r[i][0] + r[i][1] * r[i][1] + r[i][2] * r[i][2];
+        }
+        if constexpr (TAB) {
+            table_pairs<NS, double>(r2, inv_s2, tab, q, h);
+        } else {
+#pragma unroll
+            for (int i = 0; i < NS; ++i) pair64(r2[i], k, q[i], h[i]);
+        }
+#pragma unroll
+        for (int i = 0; i < NS; ++i) add(s[i], r[i], q[i], h[i], A);
+    }
+    __device__ __forceinline__ void uniform(const Part64 *__restrict__ parts, int js, int je, double tx, double ty,
+                                            double tz, Acc &A) const {
+        constexpr int NS = TAB ? 2 : 1;
+        int j = js;
+        for (; j + NS <= je; j += NS) pairs<NS>(parts + j, tx, ty, tz, A);
+        if (NS > 1 && j < je) pairs<1>(parts + j, tx, ty, tz, A);
+    }
+    __device__ __forceinline__ void grouped(const Part64 *__restrict__ parts, int js, int je, int ng, double tx,
+                                            double ty, double tz, Acc &A) const {
+#pragma unroll 1
+        for (int j = js; j < je; j += ng) pairs<1>(parts + j, tx, ty, tz, A);
+    }
+    // row K of the near sums
+    template <int K>
+    __device__ __forceinline__ double value(const Acc &A) const {
+        if constexpr (K < 3) return A.u[K] * cu;
+        else if constexpr (K < 12) return A.J[K - 3] * cj;
+        else return A.S[K - 12] * cu;
+    }
+};
+
+// Mixed precision: FP32 pair arithmetic.  Velocity sums: each block of at most
+// kKahanBlock consecutive sources is summed plainly in FP32 (up), and the block
+// sums enter the running total through Kahan's compensated addition (us, uc).
+// Per pair that is one FMA per component instead of a compensated step (4
+// instructions), and the rounding left is that of 16-term FP32 sums, around
+// 1e-7 of the block's terms.
+constexpr int kKahanBlock = 16;
+
+template <bool TAB>
+struct Pol32 {
+    using Rec = Part32;
+    using Real = float;
+    uint32_t tab;
+    float inv_s2;
+    double cu, cj;
+    Consts32 k;
+    struct Acc {
+        float us[3], uc[3], up[3], J[9], S[3];
+    };
+    static __device__ __forceinline__ void clear(Acc &A) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) A.us[c] = A.uc[c] = A.up[c] = A.S[c] = 0.0f;
+#pragma unroll
+        for (int c = 0; c < 9; ++c) A.J[c] = 0.0f;
+    }
+    __device__ __forceinline__ Pol32(double sigma, uint32_t table) : tab(table), inv_s2(0.0f), cu(1.0), cj(1.0) {
+        if constexpr (TAB) {
+            const double is = 1.0 / sigma;
+            inv_s2 = float(is * is);
+            cu = is * is * is;
+            cj = 2.0 * cu * is * is;
+        } else {
+            k = consts32(sigma);
+        }
+    }
+    static __device__ __forceinline__ void flush(Acc &A) {
+#pragma unroll
+        for (int b = 0; b < 3; ++b) {
+            const float y = A.up[b] - A.uc[b];
+            const float t = A.us[b] + y;
+            A.uc[b] = (t - A.us[b]) - y;
+            A.us[b] = t;
+            A.up[b] = 0.0f;
+        }
+    }
+    template <int NS>
+    __device__ __forceinline__ void pairs(const Part32 *__restrict__ src, float tx, float ty, float tz,
+                                          Acc &A) const {
+        Part32 s[NS];
+        float r[NS][3], r2[NS], q[NS], h[NS];
+#pragma unroll
+        for (int i = 0; i < NS; ++i) {
+            s[i] = src[i];
+            r[i][0] = tx - s[i].dx;
+            r[i][1] = ty - s[i].dy;
+            r[i][2] = tz - s[i].dz;
+            r2[i] = r[i][0] * r[i][0] + r[i][1] * r[i][1] + r[i][2] * r[i][2];
+        }
+        if constexpr (TAB) {
+            table_pairs<NS, float>(r2, inv_s2, tab, q, h);
+        } else {
+#pragma unroll
+            for (int i = 0; i < NS; ++i) pair32(r2[i], k, q[i], h[i]);
+        }
+#pragma unroll
+        for (int i = 0; i < NS; ++i) {
+            const float c[3] = {s[i].ay * r[i][2] - s[i].az * r[i][1], s[i].az * r[i][0] - s[i].ax * r[i][2],
+                                s[i].ax * r[i][1] - s[i].ay * r[i][0]};
+#pragma unroll
+            for (int b = 0; b < 3; ++b) A.up[b] = fmaf(q[i], c[b], A.up[b]);
+            A.S[0] += q[i] * s[i].ax;
+            A.S[1] += q[i] * s[i].ay;
+            A.S[2] += q[i] * s[i].az;
+            const float t0 = h[i] * c[0], t1 = h[i] * c[1], t2 = h[i] * c[2];
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                A.J[3 * d] += r[i][d] * t0;
+                A.J[3 * d + 1] += r[i][d] * t1;
+                A.J[3 * d + 2] += r[i][d] * t2;
+            }
+        }
+    }
+    __device__ __forceinline__ void uniform(const Part32 *__restrict__ parts, int js, int je, float tx, float ty,
+                                            float tz, Acc &A) const {
+        for (int jb = js; jb < je; jb += kKahanBlock) {
+            const int jend = min(jb + kKahanBlock, je);
+            int j = jb;
+            for (; j + 4 <= jend; j += 4) pairs<4>(parts + j, tx, ty, tz, A);
+            for (; j < jend; ++j) pairs<1>(parts + j, tx, ty, tz, A);
+            flush(A);
+        }
+    }
+    __device__ __forceinline__ void grouped(const Part32 *__restrict__ parts, int js, int je, int ng, float tx,
+                                            float ty, float tz, Acc &A) const {
+        // this lane group takes every ng-th source: blocks of kKahanBlock of its own sources
+        for (int jb = js; jb < je; jb += ng * kKahanBlock) {
+            const int jend = min(jb + ng * kKahanBlock, je);
+#pragma unroll 1
+            for (int j = jb; j < jend; j += ng) pairs<1>(parts + j, tx, ty, tz, A);
+            flush(A);
+        }
+    }
+    template <int K>
+    __device__ __forceinline__ double value(const Acc &A) const {
+        if constexpr (K < 3) return (double(A.us[K]) - double(A.uc[K])) * cu;
+        else if constexpr (K < 12) return double(A.J[K - 3]) * cj;
+        else return double(A.S[K - 12]) * cu;
+    }
+};
+
+template <class POL, bool SPLIT, bool TAB>
+__device__ __forceinline__ void p2p_body(const P2PArgs &a, const typename POL::Rec *__restrict__ parts) {
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    constexpr int bytes = TAB ? PairTab<typename POL::Real>::bytes : 0;
+    if constexpr (TAB) {
+        const dbl2 *src = reinterpret_cast<const dbl2 *>(a.table);
+        dbl2 *dst = reinterpret_cast<dbl2 *>(smem_raw);
+        for (int i = threadIdx.x; i < bytes / 16; i += kP2PThreads) dst[i] = src[i];
+        __syncthreads();
+    }
+    const uint32_t at = uint32_t(uintptr_t((LdsBytes)smem_raw));
+    p2p_leaves<POL, SPLIT>(a, parts, POL(a.sigma, table_base<typename POL::Real>(at)),
+                           reinterpret_cast<double *>(smem_raw + bytes));
+}
+
+template <bool SPLIT, bool TAB>
+__global__ void __launch_bounds__(kP2PThreads) __attribute__((amdgpu_waves_per_eu(TAB ? 4 : 2, TAB ? 4 : 2)))
+k_p2p64(P2PArgs a, const Part64 *__restrict__ parts) {
+    p2p_body<Pol64<TAB>, SPLIT, TAB>(a, parts);
+}
+
+template <bool SPLIT, bool TAB>
+__global__ void __launch_bounds__(kP2PThreads) __attribute__((amdgpu_waves_per_eu(6, 6)))
+k_p2p32(P2PArgs a, const Part32 *__restrict__ parts) {
+    p2p_body<Pol32<TAB>, SPLIT, TAB>(a, parts);
+}
+
+int compute_units() {
+    static const int ncu = [] {
+        int dev = 0, v = 0;
+        if (hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v < 1)
+            v = 256;
+        return v;
+    }();
+    return ncu;
+}
+
+// workgroups the chip holds at once (80 / 128 registers per lane)
+int p2p_slots(bool mixed) { return compute_units() * (mixed ? 3 : 2); }
+
+// blocks of 64 targets that a leaf holds on average, dealt over y; sources over z
+int p2p_blocks(int nleaf, int ntarget, int slots) {
+    return std::max(1, std::min(slots / nleaf, (ntarget / nleaf + 63) / 64));
+}
+
+// Leaves a wave or a workgroup takes (powers of two, as the leaf count).
+// Split: enough leaves per workgroup to make the table's copy into LDS (about 2
+// us) small beside them (a leaf 100 us), few enough to keep the launch's last
+// workgroups short.
+struct P2PShape {
+    bool split;
+    dim3 grid;
+    size_t smem;
+};
+
+P2PShape p2p_shape(const P2PArgs &a, bool mixed, int table_bytes) {
+    P2PShape s;
+    s.split = a.nleaf < kP2PSplitLeaves;
+    const int run = s.split ? (a.nleaf >= 8192 ? 4 : 1) : kP2PWaves;
+    s.grid = dim3(unsigned(a.nleaf / run), unsigned(p2p_blocks(a.nleaf, a.n, p2p_slots(mixed))),
+                  a.near ? unsigned(a.shares) : 1u);
+    s.smem = size_t(table_bytes) + (s.split ? sizeof(double) * kRedDoubles : 0);
+    return s;
+}
+
+template <typename R>
+using P2PKernel = void (*)(P2PArgs, const R *);
 
 }  // namespace
 
+int p2p_shares(int nleaf, int ntarget, bool mixed) {
+    const int slots = p2p_slots(mixed);
+    return std::max(1, std::min(8, slots / (nleaf * p2p_blocks(nleaf, ntarget, slots))));
+}
+
+// The table needs sigma-unit distances, their powers t^-3/2 and t^-5/2 and, in
+// FP32, 1/sigma^2 within the type's range.
 hipError_t launch_p2p64(hipStream_t s, const P2PArgs &a, const Part64 *parts) {
-    hipLaunchKernelGGL(k_p2p64, dim3(a.nleaf), dim3(64), 0, s, a, parts);
+    const bool tab = a.sigma >= 0x1p-100 * a.w;
+    const P2PShape p = p2p_shape(a, false, tab ? PairTab<double>::bytes : 0);
+    const P2PKernel<Part64> k = p.split ? (tab ? k_p2p64<true, true> : k_p2p64<true, false>)
+                                        : (tab ? k_p2p64<false, true> : k_p2p64<false, false>);
+    hipLaunchKernelGGL(k, p.grid, dim3(kP2PThreads), p.smem, s, a, parts);
+    return hipGetLastError();
+}
+
+hipError_t launch_p2p32(hipStream_t s, const P2PArgs &a, const Part32 *parts) {
+    const bool tab = a.sigma >= 0x1p-20 * a.w && a.sigma >= 0x1p-50 && a.sigma <= 0x1p50;
+    const P2PShape p = p2p_shape(a, true, tab ? PairTab<float>::bytes : 0);
+    const P2PKernel<Part32> k = p.split ? (tab ? k_p2p32<true, true> : k_p2p32<true, false>)
+                                        : (tab ? k_p2p32<false, true> : k_p2p32<false, false>);
+    hipLaunchKernelGGL(k, p.grid, dim3(kP2PThreads), p.smem, s, a, parts);
     return hipGetLastError();
 }
 
@@ -616,11 +1092,6 @@ hipError_t launch_p2p64_list(hipStream_t s, const P2PArgs &a, int nitem, const i
     if (nitem == 0) return hipSuccess;
     hipLaunchKernelGGL(k_p2p64_list, dim3(nitem), dim3(64), 0, s, a, nitem, items, lcell, lstart, off, cnt, meta,
                        parts);
-    return hipGetLastError();
-}
-
-hipError_t launch_p2p32(hipStream_t s, const P2PArgs &a, const Part32 *parts) {
-    hipLaunchKernelGGL(k_p2p32, dim3(a.nleaf), dim3(64), 0, s, a, parts);
     return hipGetLastError();
 }
 

@@ -15,6 +15,7 @@
 //   Mb_n^m = M_n^m N_n^m / w^n,   Lb_n^m = L_n^m w^{n+1} / N_n^m,  N_n^m = sqrt((n+m)!(n-m)!),
 // and packs the m >= 0 half of each symmetric set (F^{-m} = (-1)^m conj F^m)
 // into (p+1)^2 reals.
+#include "kernels.h"
 #include "operators.h"
 
 #include <cmath>
@@ -468,6 +469,100 @@ RecTable rec_table(int p) {
             t.c2[n * (n + 1) / 2 + m] = std::sqrt(double(n + m - 1) * double(n - m - 1) / a);
         }
     return t;
+}
+
+namespace {
+
+// Q(t) and 2 Q'(t) of the pair function
+void pair_exact(long double t, long double &q, long double &dq) {
+    const long double c = sqrtl(2.0L / acosl(-1.0L));
+    if (t < 1.0L) {
+        // g / rho^3 = sqrt(2/pi) sum (-1/2)^n / (n! (2n+3)) t^n
+        long double a = 1.0L, pw = 1.0L;   // (-1/2)^n / n!, t^n
+        q = c / 3.0L;
+        dq = 0.0L;
+        for (int n = 1; n < 30; ++n) {
+            a *= -0.5L / n;
+            dq += c * 2.0L * n * a / (2 * n + 3) * pw;
+            pw *= t;
+            q += c * a / (2 * n + 3) * pw;
+        }
+        return;
+    }
+    const long double rho = sqrtl(t), e = expl(-0.5L * t);
+    q = (erfl(rho * sqrtl(0.5L)) - c * rho * e) / (rho * t);
+    dq = (c * e - 3.0L * q) / t;
+}
+
+// coefficients [row][nc] of a table of 2^lseg segments per octave
+std::vector<long double> pair_rows_of(int lseg, int nc) {
+    constexpr int NN = 14, DM = kPairCoefs64 - 2;
+    const int R = pair_rows(lseg), D = nc - 2;   // D: degree of 2 Q'
+    std::vector<long double> out(size_t(nc) * R);
+    const long double pi = acosl(-1.0L);
+    // Chebyshev polynomials of degree <= D in monomials
+    long double T[DM + 1][DM + 1] = {};
+    T[0][0] = 1.0L;
+    T[1][1] = 1.0L;
+    for (int n = 2; n <= D; ++n)
+        for (int i = 0; i <= D; ++i) T[n][i] = (i > 0 ? 2.0L * T[n - 1][i - 1] : 0.0L) - T[n - 2][i];
+    const int seg = 1 << lseg;
+    for (int r = 0; r < R; ++r) {
+        // segment [a, b] and the centre c the kernel forms from the index bits
+        long double a, b, c;
+        const int i = r - 1;   // segment index from 2^kPairTabLo on
+        if (r > 0) {
+            const long double oct = ldexpl(1.0L, kPairTabLo + i / seg);
+            a = oct * (1.0L + (long double)(i % seg) / seg);
+            b = oct * (1.0L + (long double)(i % seg + 1) / seg);
+            c = 0.5L * (a + b);
+        } else {
+            a = 0.0L;
+            b = ldexpl(1.0L, kPairTabLo);
+            c = 0.5L * b * (1.0L + (seg - 0.5L) / seg);   // the centre of the segment just below b
+        }
+        const long double m = 0.5L * (a + b), h = 0.5L * (b - a);
+        long double v[NN], cheb[DM + 1], q, dq;
+        for (int k = 0; k < NN; ++k) pair_exact(m + h * cosl(pi * (k + 0.5L) / NN), q, v[k]);
+        for (int n = 0; n <= D; ++n) {
+            cheb[n] = 0.0L;
+            for (int k = 0; k < NN; ++k) cheb[n] += v[k] * cosl(pi * n * (k + 0.5L) / NN);
+            cheb[n] *= (n == 0 ? 1.0L : 2.0L) / NN;
+        }
+        // in y = (t - m) / h, then about x = t - c: y = (x + s) / h, s = c - m
+        long double mono[DM + 1] = {}, px[DM + 1] = {};
+        for (int n = 0; n <= D; ++n)
+            for (int k = 0; k <= n; ++k) mono[k] += cheb[n] * T[n][k];
+        const long double s = c - m;
+        for (int k = D; k >= 0; --k) {   // Horner in the polynomial (x + s) / h
+            for (int l = D; l >= 0; --l) px[l] = ((l > 0 ? px[l - 1] : 0.0L) + s * px[l]) / h;
+            px[0] += mono[k];
+        }
+        pair_exact(c, q, dq);
+        out[size_t(nc) * r] = q;
+        for (int l = 0; l <= D; ++l) out[size_t(nc) * r + l + 1] = px[l] / (2.0L * (l + 1));
+    }
+    return out;
+}
+
+}  // namespace
+
+std::vector<double> pair_table64() {
+    constexpr int nc = kPairCoefs64, R = pair_rows(kPairSeg64);
+    const std::vector<long double> c = pair_rows_of(kPairSeg64, nc);
+    std::vector<double> out(size_t(nc) * R);
+    for (int r = 0; r < R; ++r)
+        for (int l = 0; l < nc; ++l) out[(size_t(l / 2) * R + r) * 2 + l % 2] = double(c[size_t(nc) * r + l]);
+    return out;
+}
+
+std::vector<float> pair_table32() {
+    constexpr int nc = kPairCoefs32, R = pair_rows(kPairSeg32);
+    const std::vector<long double> c = pair_rows_of(kPairSeg32, nc);
+    std::vector<float> out(size_t(8) * R, 0.0f);
+    for (int r = 0; r < R; ++r)
+        for (int l = 0; l < nc; ++l) out[(size_t(l / 4) * R + r) * 4 + l % 4] = float(c[size_t(nc) * r + l]);
+    return out;
 }
 
 }  // namespace vmfmm

@@ -96,4 +96,13 @@ struct RecTable {
 };
 RecTable rec_table(int p);
 
+// Tables of the pair function (layouts: kernels.h): Q(t) = (erf(s) - sqrt(2/pi) rho
+// exp(-rho^2/2)) / rho^3 with t = rho^2, s = rho / sqrt2, per segment of t a
+// polynomial in x = t - (segment centre) whose doubled derivative is the
+// truncated Chebyshev series of 2 Q'(t) over the segment and whose value at
+// the centre is Q's.  Evaluated in extended precision (long double), from the
+// power series below t = 1.
+std::vector<double> pair_table64();
+std::vector<float> pair_table32();
+
 }  // namespace vmfmm

@@ -204,7 +204,7 @@ struct vm_ctx {
     // operator caches
     std::map<int, std::unique_ptr<OpSet>> ops;
     std::map<std::pair<int, int>, std::unique_ptr<DevBuf>> lattice;
-    DevBuf offsets, octlists;
+    DevBuf offsets, octlists, pair_tab64, pair_tab32;
     bool tables_ready = false;
 };
 
@@ -276,6 +276,8 @@ vm_status ensure_tables(vm_ctx *ctx) {
     const std::vector<int16_t> lists = device_octant_lists();
     VM_HIP(upload(ctx->offsets, offs), "upload offsets");
     VM_HIP(upload(ctx->octlists, lists), "upload octant lists");
+    VM_HIP(upload(ctx->pair_tab64, pair_table64()), "upload pair table");
+    VM_HIP(upload(ctx->pair_tab32, pair_table32()), "upload pair table");
     ctx->tables_ready = true;
     return VM_OK;
 }
@@ -687,8 +689,7 @@ vm_status build_tree(vm_ctx *ctx, const TreeBufs &b, int ni, const double *x, co
     VM_HIP(b.vals_b->reserve(sizeof(int32_t) * n), "alloc perm");
     VM_HIP(ctx->hist.reserve(sizeof(uint32_t) * radix_hist_words(ni)), "alloc histogram");
     VM_HIP(b.start->reserve(sizeof(int32_t) * size_t(nleaf + 1)), "alloc leaf ranges");
-    // one record to spare: the FP32 P2P prefetches one record past a block's end
-    if (mixed) VM_HIP(b.p32->reserve(sizeof(Part32) * (size_t(n) + 1)), "alloc particles");
+    if (mixed) VM_HIP(b.p32->reserve(sizeof(Part32) * n), "alloc particles");
     else VM_HIP(b.p64->reserve(sizeof(Part64) * n), "alloc particles");
 
     int32_t *start = b.start->as<int32_t>();
@@ -923,7 +924,8 @@ vm_status fmm_impl(vm_ctx *ctx, int64_t n, const double *x, const double *alpha,
     const size_t esz = mixed ? sizeof(float) : sizeof(double);
     const int64_t ncells = ((int64_t(1) << (3 * (level + 1))) - 1) / 7;
     VM_HIP(ctx->far.reserve(sizeof(double) * 12 * size_t(mi)), "alloc far field");
-    VM_HIP(ctx->nearf.reserve(sizeof(double) * 15 * size_t(mi)), "alloc near field");
+    const int shares = p2p_shares(int(nleaf), mi, mixed);
+    VM_HIP(ctx->nearf.reserve(sizeof(double) * 15 * size_t(mi) * shares), "alloc near field");
     VM_HIP(ctx->trpart.reserve(kTrPartBytes), "alloc split partials");
     if (ctx->zeros.bytes == 0) VM_HIP(ctx->zeros.reserve(tr_zero_elems(coef_stride(ncoef(VM_MAX_P))) * sizeof(double), true),
                                       "alloc zero cell");
@@ -989,6 +991,7 @@ vm_status fmm_impl(vm_ctx *ctx, int64_t n, const double *x, const double *alpha,
     a.perm = tperm;
     a.alpha = alpha;
     a.far = ctx->far.as<double>();
+    a.table = mixed ? ctx->pair_tab32.ptr : ctx->pair_tab64.ptr;
     a.u = u;
     a.dalpha = y ? nullptr : dalpha_dt;
     a.grad = grad;
@@ -1004,6 +1007,7 @@ vm_status fmm_impl(vm_ctx *ctx, int64_t n, const double *x, const double *alpha,
         P2PArgs an = a;
         an.have_far = 0;
         an.near = ctx->nearf.as<double>();
+        an.shares = shares;
         VM_HIP(hipEventRecord(ctx->ev_fork, s), "fork");
         VM_HIP(hipStreamWaitEvent(ctx->side, ctx->ev_fork, 0), "fork");
         if (vm_status st = near_field(ctx->side, an); st != VM_OK) return st;
@@ -1088,6 +1092,7 @@ vm_status fmm_impl(vm_ctx *ctx, int64_t n, const double *x, const double *alpha,
             VM_HIP(hipStreamWaitEvent(s, ctx->ev_join, 0), "join");
             NearCombine nc;
             nc.near = ctx->nearf.as<double>();
+            nc.shares = shares;
             nc.perm = tperm;
             nc.alpha = alpha;
             nc.u = u;
@@ -1697,7 +1702,7 @@ vm_status adjoint_impl(vm_ctx *ctx, int64_t n, const double *x, const double *al
     VM_HIP(ctx->adj_v.reserve(v3), "alloc adjoint");
     VM_HIP(ctx->adj_Jv.reserve(v9), "alloc adjoint");
     VM_HIP(ctx->adj_far.reserve(2 * v3), "alloc adjoint");
-    if (mixed) VM_HIP(ctx->adj_p32.reserve(sizeof(Part32) * (size_t(n) + 1)), "alloc adjoint");
+    if (mixed) VM_HIP(ctx->adj_p32.reserve(sizeof(Part32) * size_t(n)), "alloc adjoint");
     else VM_HIP(ctx->adj_p64.reserve(sizeof(Part64) * n), "alloc adjoint");
     const int32_t *start = ctx->start.as<int32_t>();
     const int32_t *perm = ctx->last_perm;
@@ -1788,6 +1793,7 @@ vm_status adjoint_impl(vm_ctx *ctx, int64_t n, const double *x, const double *al
     a.perm = perm;
     a.alpha = nullptr;
     a.far = nullptr;
+    a.table = mixed ? ctx->pair_tab32.ptr : ctx->pair_tab64.ptr;
     a.u = ctx->adj_v.as<double>();
     a.dalpha = nullptr;
     a.grad = ctx->adj_Jv.as<double>();
