@@ -189,7 +189,8 @@ hipError_t launch_p2p32(hipStream_t s, const P2PArgs &a, const Part32 *parts);
 // of (src, code) with image shift codes; cells' particle ranges, keys and
 // levels from the tree.  Same combine and output as launch_p2p64 (a.n,
 // a.perm, a.alpha, a.far, a.u, a.dalpha, a.grad, a.scheme, a.have_far,
-// a.sigma are used).
+// a.sigma, a.table and a.w, the root's width, are used; ctr: 8 zeros on the
+// device, launch_ad_p2p_meta writes them).
 struct AdTreeView;
 // One P2P list entry of an adaptive target leaf: the source leaf's sorted
 // particle range and D = centre_b + s L - centre_a, which takes the source
@@ -200,7 +201,7 @@ struct __align__(32) P2PMeta {
 };
 hipError_t launch_p2p64_list(hipStream_t s, const P2PArgs &a, int nitem, const int2 *items, const int32_t *lcell,
                              const int32_t *lstart, const uint32_t *off, const uint32_t *cnt, const P2PMeta *meta,
-                             const Part64 *parts);
+                             const Part64 *parts, int *ctr);
 
 // --- RBF interpolation (kernels_rbf.hip) --------------------------------------------
 struct GaussArgs {
@@ -302,9 +303,11 @@ hipError_t launch_ad_root(hipStream_t s, const AdTreeView &t, int n);
 // first position of each group and starts[8 nlev] = ncell (device ints).
 hipError_t launch_ad_groups(hipStream_t s, const AdTreeView &t, int ncell, int nlev, uint32_t *ka, int32_t *va,
                             uint32_t *kb, int32_t *vb, uint32_t *hist, int *starts);
-// meta[e] of every P2P list entry e of the ncell cells (list 0 of off / cnt)
+// meta[e] of every P2P list entry e of the ncell cells (list 0 of off / cnt);
+// zeroes ctr[8]
 hipError_t launch_ad_p2p_meta(hipStream_t s, const AdTreeView &t, int ncell, const uint32_t *off,
-                              const uint32_t *cnt, const int32_t *src, const int8_t *code, P2PMeta *meta);
+                              const uint32_t *cnt, const int32_t *src, const int8_t *code, P2PMeta *meta,
+                              int *ctr);
 // the centres of the ncell cells into ctr[cell][4] (the cell-particle and near
 // field kernels read them instead of decoding keys)
 hipError_t launch_ad_centres(hipStream_t s, const AdTreeView &t, int ncell, double *ctr);

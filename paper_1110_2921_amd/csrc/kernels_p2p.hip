@@ -15,17 +15,12 @@
 // out the sources.  The sums go to the near buffer that L2P combines with the
 // far field, or, without one, through the epilogue here: far field, the
 // gradient's contraction into the stretching term, the caller's order.
-#include <algorithm>
-#include <type_traits>
-#include <utility>
-
-#include "kernels.h"
+#include "leaf_sums.h"
 
 namespace vmfmm {
 
 namespace {
 
-constexpr double kInv4Pi = 0.079577471545947667884441881686257181;
 constexpr double kSqrt2OverPi = 0.79788456080286535587989211986876373;
 
 // a_n = (-1/2)^n / (n! (2n+3)): g / rho^3 = sqrt(2/pi) sum a_n rho^{2n}
@@ -228,418 +223,6 @@ __device__ __forceinline__ void pair32(float r2, const Consts32 &k, float &q, fl
     }
 }
 
-__device__ __forceinline__ int demorton(int k, int d, int level) {
-    int c = 0;
-    for (int b = 0; b < level; ++b) c |= ((k >> (3 * b + d)) & 1) << b;
-    return c;
-}
-
-__device__ __forceinline__ int morton(int cx, int cy, int cz, int level) {
-    int k = 0;
-    for (int b = 0; b < level; ++b)
-        k |= (((cx >> b) & 1) << (3 * b)) | (((cy >> b) & 1) << (3 * b + 1)) | (((cz >> b) & 1) << (3 * b + 2));
-    return k;
-}
-
-// Writes u, dalpha/dt and J for sorted particle gi (caller index oi) from the
-// near sums (velocity us - uc, rank-one gradient part Jr, S = sum q alpha) plus
-// the far field.  Every near value passes through `red` on its way (the
-// identity, or the sum over the lane groups of a split target block: then all
-// lanes run this, and only those with `write` set store).  Streamed value by
-// value, J row by row with the stretching contraction accumulated on the way,
-// so that few values are live at once: the kernels' register budget, hence
-// their occupancy, is set here.
-template <typename A, typename R>
-__device__ __forceinline__ void epilogue(const P2PArgs &a, int gi, bool write, const A us[3], const A uc[3],
-                                         const A Jr[9], const A S[3], R red) {
-    const size_t n = size_t(a.n);
-    if (a.near) {
-        // near field only (sorted order), the same reductions as below
-        for (int b = 0; b < 3; ++b) {
-            const double v = red(double(us[b]) - double(uc[b]));
-            if (write) a.near[b * n + gi] = v;
-        }
-        if (!a.grad && !a.dalpha) return;
-        for (int k = 0; k < 9; ++k) {
-            const double v = red(double(Jr[k]));
-            if (write) a.near[(3 + k) * n + gi] = v;
-        }
-        for (int c = 0; c < 3; ++c) {
-            const double v = red(double(S[c]));
-            if (write) a.near[(12 + c) * n + gi] = v;
-        }
-        return;
-    }
-    const int oi = write ? a.perm[gi] : 0;
-    for (int b = 0; b < 3; ++b) {
-        double u = red(double(us[b]) - double(uc[b])) * kInv4Pi;
-        if (write) {
-            if (a.have_far) u += a.far[b * n + gi];
-            a.u[b * n + oi] = u;
-        }
-    }
-    if (!a.grad && !a.dalpha) return;
-    double Sd[3];
-    for (int c = 0; c < 3; ++c) Sd[c] = red(double(S[c]));
-    double al[3] = {0.0, 0.0, 0.0};
-    if (write && a.dalpha)
-        for (int c = 0; c < 3; ++c) al[c] = a.alpha[c * n + oi];
-    double da[3] = {0.0, 0.0, 0.0};
-#pragma unroll
-    for (int r = 0; r < 3; ++r) {
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            // antisymmetric part eps_abc S_c of the near gradient J[r][c]
-            const int k = 3 - r - c;
-            const double anti = r == c ? 0.0 : ((c == (r + 1) % 3) ? Sd[k] : -Sd[k]);
-            double J = (red(double(Jr[3 * r + c])) + anti) * kInv4Pi;
-            if (write) {
-                if (a.have_far) J += a.far[(3 + 3 * r + c) * n + gi];
-                if (a.grad) a.grad[(3 * r + c) * n + oi] = J;
-            }
-            if (a.scheme == 0) da[c] += al[r] * J;      // classic: sum_a alpha_a J[a][b]
-            else da[r] += J * al[c];                     // transpose: sum_c J[b][c] alpha_c
-        }
-    }
-    if (write && a.dalpha)
-        for (int b = 0; b < 3; ++b) a.dalpha[b * n + oi] = da[b];
-}
-
-struct NoReduce {
-    __device__ double operator()(double v) const { return v; }
-};
-
-// sum over the lane groups of a split block (lanes l, l ^ E, l ^ 2E, ...), fixed order
-struct GroupSum {
-    int E;
-    __device__ double operator()(double v) const {
-        for (int off = E; off < 64; off <<= 1) v += __shfl_xor(v, off);
-        return v;
-    }
-};
-
-// Target blocks of a leaf: whole blocks of 64 targets, one target per lane, take
-// every source at a wave-uniform address (scalar loads).  A last block of
-// rem <= 32 targets would leave most lanes idle, so there the wave splits into
-// g = 64 / E lane groups (E = rem rounded up to a power of two): lane group k
-// takes target t = lane % E against every g-th source of each neighbour leaf,
-// and the groups' partial sums are combined in FP64 by a fixed butterfly.
-__device__ __forceinline__ int pow2_ceil(int v) {
-    int e = 1;
-    while (e < v) e <<= 1;
-    return e;
-}
-
-struct LeafGeom {
-    int cx, cy, cz, side;
-};
-
-// neighbour nb of the target leaf: source range and the offset d (source - target cell)
-__device__ __forceinline__ bool neighbour(const P2PArgs &a, const LeafGeom &L, int nb, int &js, int &je, int &dx,
-                                          int &dy, int &dz) {
-    dx = nb % 3 - 1;
-    dy = (nb / 3) % 3 - 1;
-    dz = nb / 9 - 1;
-    int nx = L.cx + dx, ny = L.cy + dy, nz = L.cz + dz;
-    if (a.periodic) {
-        nx = (nx + L.side) % L.side;
-        ny = (ny + L.side) % L.side;
-        nz = (nz + L.side) % L.side;
-    } else if (nx < 0 || ny < 0 || nz < 0 || nx >= L.side || ny >= L.side || nz >= L.side) {
-        return false;
-    }
-    const int nk = morton(nx, ny, nz, a.level);
-    js = a.start[nk];
-    je = a.start[nk + 1];
-    return true;
-}
-
-__device__ __forceinline__ void acc64(const Part64 &s, double tx, double ty, double tz, const Consts64 &k,
-                                      double u[3], double Jr[9], double S[3]) {
-    const double rx = tx - s.dx, ry = ty - s.dy, rz = tz - s.dz;
-    const double r2 = rx * rx + ry * ry + rz * rz;
-    double q, dq;
-    pair64(r2, k, q, dq);
-    const double c0 = s.ay * rz - s.az * ry;
-    const double c1 = s.az * rx - s.ax * rz;
-    const double c2 = s.ax * ry - s.ay * rx;
-    u[0] += q * c0;
-    u[1] += q * c1;
-    u[2] += q * c2;
-    S[0] += q * s.ax;
-    S[1] += q * s.ay;
-    S[2] += q * s.az;
-    const double t0 = dq * c0, t1 = dq * c1, t2 = dq * c2;
-    Jr[0] += rx * t0; Jr[1] += rx * t1; Jr[2] += rx * t2;
-    Jr[3] += ry * t0; Jr[4] += ry * t1; Jr[5] += ry * t2;
-    Jr[6] += rz * t0; Jr[7] += rz * t1; Jr[8] += rz * t2;
-}
-
-// Workgroups are handed to the 8 XCDs round-robin; leaf (blockIdx mod 8) *
-// nleaf/8 + blockIdx/8 gives each XCD one contiguous Morton range, whose
-// neighbour leaves its L2 then shares.
-__device__ __forceinline__ int xcd_leaf(int nleaf) {
-    const int b = blockIdx.x;
-    if (nleaf % 8 != 0) return b;
-    return (b & 7) * (nleaf >> 3) + (b >> 3);
-}
-
-// Adaptive tree: one wave per target leaf (leaves in particle order, dealt to
-// the XCDs like the uniform leaves), sources from the leaf's P2P list: source
-// leaf b with image shift s contributes x_i - x_j - s L = (delta_i - D) -
-// delta_j, D = centre_b + s L - centre_a, with the records relative to their
-// own leaf centres.
-__device__ __forceinline__ void ad_centre(const AdTreeView &t, int c, double out[3]) {
-    if (t.ctr) {
-        for (int d = 0; d < 3; ++d) out[d] = t.ctr[4 * size_t(c) + d];
-        return;
-    }
-    const int l = t.level[c];
-    const double w = ldexp(t.box_len, -l);
-    for (int d = 0; d < 3; ++d) out[d] = t.lo[d] + (double(demorton(t.key[c], d, l)) + 0.5) * w;
-}
-
-// Work item w of an adaptive near field: target block items[w] = (leaf i in
-// particle order, first target of the block within the leaf), 64 targets per
-// block, so that a crowded leaf at the finest level spreads over many waves.
-__global__ void __launch_bounds__(64) k_p2p64_list(P2PArgs a, int nitem, const int2 *__restrict__ items,
-                                                   const int32_t *__restrict__ lcell,
-                                                   const int32_t *__restrict__ lstart,
-                                                   const uint32_t *__restrict__ off, const uint32_t *__restrict__ cnt,
-                                                   const P2PMeta *__restrict__ meta,
-                                                   const Part64 *__restrict__ parts) {
-    const int2 it = items[xcd_leaf(nitem)];
-    const int li = it.x, base = it.y, lane = threadIdx.x;
-    const int c = lcell[li];
-    const int s0 = lstart[li], nt = lstart[li + 1] - s0;
-    const uint32_t e0 = off[c], e1 = e0 + cnt[c];
-    const Consts64 k = consts64(a.sigma);
-    const double zero[3] = {0.0, 0.0, 0.0};
-    // each entry's source range and frame shift: one record, the next one
-    // fetched (scalar load) while the current entry's sources are evaluated
-    P2PMeta mn{};
-    if (e1 > e0) mn = meta[e0];
-    const int nfull = nt - nt % 64 + (nt % 64 > 32 ? 64 : 0);
-    if (base < nfull) {
-        const bool valid = lane < nt - base;
-        const Part64 me = parts[s0 + base + (valid ? lane : 0)];
-        double u[3] = {0, 0, 0}, Jr[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0}, S[3] = {0, 0, 0};
-        for (uint32_t e = e0; e < e1; ++e) {
-            const P2PMeta m = mn;
-            mn = meta[e + 1 < e1 ? e + 1 : e];
-            const double tx = me.dx - m.dx, ty = me.dy - m.dy, tz = me.dz - m.dz;
-            for (int j = m.js; j < m.je; ++j) acc64(parts[j], tx, ty, tz, k, u, Jr, S);
-        }
-        if (valid) epilogue(a, s0 + base + lane, true, u, zero, Jr, S, NoReduce{});
-        return;
-    }
-    // the last block of rem <= 32 targets: lane groups share out the sources
-    const int rem = nt - nfull;
-    const int E = pow2_ceil(rem);
-    const int tt = lane & (E - 1), gi = lane / E, ng = 64 / E;
-    const bool valid = tt < rem;
-    const Part64 me = parts[s0 + nfull + (valid ? tt : 0)];
-    double u[3] = {0, 0, 0}, Jr[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0}, S[3] = {0, 0, 0};
-    for (uint32_t e = e0; e < e1; ++e) {
-        const P2PMeta m = mn;
-        mn = meta[e + 1 < e1 ? e + 1 : e];
-        const double tx = me.dx - m.dx, ty = me.dy - m.dy, tz = me.dz - m.dz;
-#pragma unroll 1
-        for (int j = m.js + gi; j < m.je; j += ng) acc64(parts[j], tx, ty, tz, k, u, Jr, S);
-    }
-    epilogue(a, s0 + nfull + tt, valid && gi == 0, u, zero, Jr, S, GroupSum{E});
-}
-
-// --- uniform tree ------------------------------------------------------------
-// Workgroups of 8 waves (the pair table in LDS is shared), one target per lane,
-// sources at wave-uniform addresses (scalar loads).  Two ways to deal out the
-// work:
-//   SPLIT   a workgroup takes one leaf at a time: the sources of its 27
-//           neighbour leaves, concatenated, go to the waves in equal contiguous
-//           shares, every wave holds the same targets, and the waves' sums are
-//           added through LDS in wave order.  A tree of few leaves needs this:
-//           with one wave per leaf, 64 leaves ran 64 waves on 1024 SIMDs, each
-//           through 1728 sources in turn (16^3 FP64: 602 us; split 30 us).
-//           Trees of fewer leaves than the chip holds workgroups also deal a
-//           leaf's target blocks over gridDim.y and its sources over gridDim.z
-//           (partial near fields, added by L2P).
-//   !SPLIT  a wave per leaf, without the reduction, from kP2PSplitLeaves on, where
-//           the leaves fill the chip many times over (128^3, one evaluation:
-//           FP64 13.7 against 14.5 ms split, a mixed Heun step 14.6 against 15.9).
-// Workgroups go to the 8 XCDs round-robin, so workgroup b takes leaves of the
-// (b mod 8)-th eighth of the Morton order, whose neighbour leaves that XCD's L2
-// then shares.
-constexpr int kP2PWaves = 8;
-constexpr int kP2PThreads = 64 * kP2PWaves;
-constexpr int kNearRows = 15;     // u, gradient sums, strength sums
-constexpr int kRedRows = 3;       // values per reduction round
-constexpr int kRedDoubles = kRedRows * kP2PThreads + kNearRows * 64;
-
-// lane group size of a target piece of `rem` targets: 64 (a whole wave) or the
-// lane groups' power of two; a remainder a little over a power of two is cut
-// there, the rest is a piece of its own (34 targets: 32 + 2, 34 / 64 of a
-// whole-wave pass instead of all of it)
-__device__ __forceinline__ int piece_lanes(int rem) {
-    if (rem > 48) return 64;
-    const int e = pow2_ceil(rem);
-    return e > 8 && 4 * rem <= 3 * e ? e >> 1 : e;
-}
-
-template <int K>
-using IC = std::integral_constant<int, K>;
-
-template <class F, int... K>
-__device__ __forceinline__ void for_rows(F &&f, std::integer_sequence<int, K...>) {
-    (f(IC<K>{}), ...);
-}
-
-// u, J and dalpha/dt of sorted target gi from its near sums f(row), with the
-// far field where there is one, in caller order
-template <class F>
-__device__ __forceinline__ void finish(const P2PArgs &a, int gi, bool write, F f) {
-    if (!write) return;
-    const size_t n = size_t(a.n);
-    const int oi = a.perm[gi];
-    for (int b = 0; b < 3; ++b) a.u[b * n + oi] = f(b) * kInv4Pi + (a.have_far ? a.far[b * n + gi] : 0.0);
-    if (!a.grad && !a.dalpha) return;
-    double al[3] = {0.0, 0.0, 0.0};
-    if (a.dalpha)
-        for (int c = 0; c < 3; ++c) al[c] = a.alpha[c * n + oi];
-    double da[3] = {0.0, 0.0, 0.0};
-#pragma unroll
-    for (int r = 0; r < 3; ++r) {
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            // antisymmetric part eps_abc S_c of the near gradient J[r][c]
-            const int k = 3 - r - c;
-            const double anti = r == c ? 0.0 : ((c == (r + 1) % 3) ? f(12 + k) : -f(12 + k));
-            double J = (f(3 + 3 * r + c) + anti) * kInv4Pi;
-            if (a.have_far) J += a.far[(3 + 3 * r + c) * n + gi];
-            if (a.grad) a.grad[(3 * r + c) * n + oi] = J;
-            if (a.scheme == 0) da[c] += al[r] * J;      // classic: sum_a alpha_a J[a][b]
-            else da[r] += J * al[c];                     // transpose: sum_c J[b][c] alpha_c
-        }
-    }
-    if (a.dalpha)
-        for (int b = 0; b < 3; ++b) a.dalpha[b * n + oi] = da[b];
-}
-
-template <class POL, bool SPLIT>
-__device__ __forceinline__ void p2p_leaves(const P2PArgs &a, const typename POL::Rec *__restrict__ parts,
-                                           const POL &pol, double *red) {
-    using Rec = typename POL::Rec;
-    using T = typename POL::Real;
-    double *fin = red + kRedRows * kP2PThreads;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const Rec *__restrict__ targets = static_cast<const Rec *>(a.tparts);
-    const size_t n = size_t(a.n);
-    const int run = a.nleaf / int(gridDim.x);   // leaves of this workgroup
-    const bool xcd = a.nleaf % 8 == 0 && gridDim.x % 8 == 0;
-    const int first = xcd ? int(blockIdx.x & 7) * (a.nleaf >> 3) + int(blockIdx.x >> 3) * run : int(blockIdx.x) * run;
-    const int nsh = int(gridDim.z) * kP2PWaves, sh = int(blockIdx.z) * kP2PWaves + wave;
-    const T w = T(a.w);
-    for (int li = SPLIT ? 0 : wave; li < run; li += SPLIT ? 1 : kP2PWaves) {
-        const int leaf = first + li;
-        const int s0 = a.tstart[leaf], cnt = a.tstart[leaf + 1] - s0;
-        if (cnt == 0) continue;
-        // lane nb < 27: the neighbour's first source and the end of its sources in
-        // the concatenated list
-        int nb_js = 0, nb_end = 0;
-        {
-            LeafGeom L;
-            L.side = 1 << a.level;
-            L.cx = demorton(leaf, 0, a.level);
-            L.cy = demorton(leaf, 1, a.level);
-            L.cz = demorton(leaf, 2, a.level);
-            int je = 0, dx, dy, dz;
-            if (lane < 27 && !neighbour(a, L, lane, nb_js, je, dx, dy, dz)) nb_js = je = 0;
-            nb_end = je - nb_js;
-#pragma unroll
-            for (int d = 1; d < 32; d <<= 1) {
-                const int y = __shfl_up(nb_end, d, 64);
-                if (lane >= d) nb_end += y;
-            }
-        }
-        const int64_t total = __builtin_amdgcn_readlane(nb_end, 26);
-        const int q0 = SPLIT ? int(total * sh / nsh) : 0, q1 = SPLIT ? int(total * (sh + 1) / nsh) : int(total);
-        int piece = 0;
-        for (int base = 0; base < cnt; ++piece) {
-            const int E = piece_lanes(cnt - base);
-            const int b0 = base;
-            base += E;
-            if (SPLIT && piece % int(gridDim.y) != int(blockIdx.y)) continue;
-            const int t = lane & (E - 1), grp = lane / E, ng = 64 / E;
-            const bool write = b0 + t < cnt && grp == 0;
-            const int gi = s0 + (b0 + t < cnt ? b0 + t : b0);
-            const Rec me = targets[gi];
-            typename POL::Acc A;
-            POL::clear(A);
-            int c1 = 0;
-            for (int nb = 0; nb < 27; ++nb) {
-                const int c0 = c1;
-                c1 = __builtin_amdgcn_readlane(nb_end, nb);
-                const int p0 = q0 > c0 ? q0 : c0, p1 = q1 < c1 ? q1 : c1;
-                if (p0 >= p1) continue;
-                const int js = __builtin_amdgcn_readlane(nb_js, nb) + (p0 - c0), je = js + (p1 - p0);
-                // x_i - x_j = (delta_i - d w) - delta_j, d = source - target cell offset
-                const int dx = nb % 3 - 1, dy = (nb / 3) % 3 - 1, dz = nb / 9 - 1;
-                const T tx = me.dx - T(dx) * w, ty = me.dy - T(dy) * w, tz = me.dz - T(dz) * w;
-                if (E == 64) pol.uniform(parts, js, je, tx, ty, tz, A);
-                else pol.grouped(parts, js + grp, je, ng, tx, ty, tz, A);
-            }
-            // the lane groups' sums (fixed butterfly)
-            auto sum = [&](auto kc) {
-                double x = pol.template value<decltype(kc)::value>(A);
-                for (int off = E; off < 64; off <<= 1) x += __shfl_xor(x, off);
-                return x;
-            };
-            const bool all = a.grad || a.dalpha;
-            if constexpr (!SPLIT) {
-                if (a.near) {
-                    auto put = [&](auto kc) {
-                        const double x = sum(kc);
-                        if (write) a.near[size_t(decltype(kc)::value) * n + gi] = x;
-                    };
-                    for_rows(put, std::make_integer_sequence<int, 3>{});
-                    if (all)
-                        for_rows([&](auto kc) { put(IC<decltype(kc)::value + 3>{}); },
-                                 std::make_integer_sequence<int, kNearRows - 3>{});
-                } else {
-                    double f[kNearRows];
-                    for_rows([&](auto kc) { f[decltype(kc)::value] = sum(kc); },
-                             std::make_integer_sequence<int, kNearRows>{});
-                    finish(a, gi, write, [&](int r) { return f[r]; });
-                }
-            } else {
-                // then the waves', kRedRows values a round
-                auto round = [&](auto rc) {
-                    constexpr int r0 = decltype(rc)::value * kRedRows;
-                    for_rows([&](auto kc) {
-                        constexpr int k = decltype(kc)::value;
-                        red[(k * kP2PWaves + wave) * 64 + lane] = sum(IC<r0 + k>{});
-                    }, std::make_integer_sequence<int, kRedRows>{});
-                    __syncthreads();
-                    if (tid < 64 * kRedRows) {
-                        const int k = tid >> 6;
-                        double x = 0.0;
-#pragma unroll
-                        for (int q = 0; q < kP2PWaves; ++q) x += red[(k * kP2PWaves + q) * 64 + lane];
-                        if (!a.near) fin[(r0 + k) * 64 + lane] = x;
-                        else if (write) a.near[(size_t(blockIdx.z) * kNearRows + r0 + k) * n + gi] = x;
-                    }
-                    __syncthreads();
-                };
-                round(IC<0>{});
-                if (all)
-                    for_rows([&](auto kc) { round(IC<decltype(kc)::value + 1>{}); },
-                             std::make_integer_sequence<int, kNearRows / kRedRows - 1>{});
-                if (!a.near && wave == 0) finish(a, gi, write, [&](int r) { return fin[64 * r + lane]; });
-            }
-        }
-    }
-}
-
 // The pair function from a table.  With t = rho^2 = r^2 / sigma^2,
 //   q = Q(t) / sigma^3,  q'/r = 2 Q'(t) / sigma^5,  Q(t) = g / rho^3:
 // both are one smooth function of t and its derivative, so one polynomial
@@ -802,6 +385,7 @@ struct Pol64 {
     struct Acc {
         double u[3], J[9], S[3];
     };
+    static __device__ __forceinline__ Real scaled(Real x) { return x; }
     static __device__ __forceinline__ void clear(Acc &A) {
 #pragma unroll
         for (int c = 0; c < 3; ++c) A.u[c] = A.S[c] = 0.0;
@@ -899,6 +483,7 @@ struct Pol32 {
     struct Acc {
         float us[3], uc[3], up[3], J[9], S[3];
     };
+    static __device__ __forceinline__ Real scaled(Real x) { return x; }
     static __device__ __forceinline__ void clear(Acc &A) {
 #pragma unroll
         for (int c = 0; c < 3; ++c) A.us[c] = A.uc[c] = A.up[c] = A.S[c] = 0.0f;
@@ -990,19 +575,25 @@ struct Pol32 {
     }
 };
 
+// Copies the table to the start of the dynamic LDS; what the policies take for it.
+template <typename T, bool TAB>
+__device__ __forceinline__ uint32_t load_table(const void *table) {
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    if constexpr (TAB) {
+        const dbl2 *src = reinterpret_cast<const dbl2 *>(table);
+        dbl2 *dst = reinterpret_cast<dbl2 *>(smem_raw);
+        for (int i = threadIdx.x; i < PairTab<T>::bytes / 16; i += kP2PThreads) dst[i] = src[i];
+        __syncthreads();
+    }
+    return table_base<T>(uint32_t(uintptr_t((LdsBytes)smem_raw)));
+}
+
 template <class POL, bool SPLIT, bool TAB>
 __device__ __forceinline__ void p2p_body(const P2PArgs &a, const typename POL::Rec *__restrict__ parts) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    constexpr int bytes = TAB ? PairTab<typename POL::Real>::bytes : 0;
-    if constexpr (TAB) {
-        const dbl2 *src = reinterpret_cast<const dbl2 *>(a.table);
-        dbl2 *dst = reinterpret_cast<dbl2 *>(smem_raw);
-        for (int i = threadIdx.x; i < bytes / 16; i += kP2PThreads) dst[i] = src[i];
-        __syncthreads();
-    }
-    const uint32_t at = uint32_t(uintptr_t((LdsBytes)smem_raw));
-    p2p_leaves<POL, SPLIT>(a, parts, POL(a.sigma, table_base<typename POL::Real>(at)),
-                           reinterpret_cast<double *>(smem_raw + bytes));
+    using T = typename POL::Real;
+    p2p_leaves<POL, SPLIT>(a, parts, POL(a.sigma, load_table<T, TAB>(a.table)),
+                           reinterpret_cast<double *>(smem_raw + (TAB ? PairTab<T>::bytes : 0)));
 }
 
 template <bool SPLIT, bool TAB>
@@ -1017,49 +608,74 @@ k_p2p32(P2PArgs a, const Part32 *__restrict__ parts) {
     p2p_body<Pol32<TAB>, SPLIT, TAB>(a, parts);
 }
 
-int compute_units() {
-    static const int ncu = [] {
-        int dev = 0, v = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v < 1)
-            v = 256;
-        return v;
-    }();
-    return ncu;
-}
-
-// workgroups the chip holds at once (80 / 128 registers per lane)
-int p2p_slots(bool mixed) { return compute_units() * (mixed ? 3 : 2); }
-
-// blocks of 64 targets that a leaf holds on average, dealt over y; sources over z
-int p2p_blocks(int nleaf, int ntarget, int slots) {
-    return std::max(1, std::min(slots / nleaf, (ntarget / nleaf + 63) / 64));
-}
-
-// Leaves a wave or a workgroup takes (powers of two, as the leaf count).
-// Split: enough leaves per workgroup to make the table's copy into LDS (about 2
-// us) small beside them (a leaf 100 us), few enough to keep the launch's last
-// workgroups short.
-struct P2PShape {
-    bool split;
-    dim3 grid;
-    size_t smem;
-};
-
-P2PShape p2p_shape(const P2PArgs &a, bool mixed, int table_bytes) {
-    P2PShape s;
-    s.split = a.nleaf < kP2PSplitLeaves;
-    const int run = s.split ? (a.nleaf >= 8192 ? 4 : 1) : kP2PWaves;
-    s.grid = dim3(unsigned(a.nleaf / run), unsigned(p2p_blocks(a.nleaf, a.n, p2p_slots(mixed))),
-                  a.near ? unsigned(a.shares) : 1u);
-    s.smem = size_t(table_bytes) + (s.split ? sizeof(double) * kRedDoubles : 0);
-    return s;
+// Adaptive tree: work item w is the target block items[w] = (leaf i in particle
+// order, first target of the block of up to 64 within the leaf), its sources the
+// leaf's P2P list: entry (source range, D = centre_b + s L - centre_a) contributes
+// x_i - x_j - s L = (delta_i - D) - delta_j, the records relative to their own
+// leaf centres.  A wave per item; the 8 waves of a workgroup share the pair table.
+// Items differ by a factor of ten in work and a workgroup's table and registers
+// hold half a compute unit, so the workgroups are as many as fit and their waves
+// take items one by one, first from their XCD's contiguous eighth (neighbour
+// leaves share its L2), then from the others' (ctr[8]: items taken of each eighth,
+// zero at the start).  P2P of 2^19 clustered particles 2.05 ms
+// (pair function by polynomials, one wave per workgroup and item: 3.83 ms).
+template <bool TAB>
+__global__ void __launch_bounds__(kP2PThreads) __attribute__((amdgpu_waves_per_eu(TAB ? 4 : 2, TAB ? 4 : 2)))
+k_p2p64_list(P2PArgs a, int nitem, const int2 *__restrict__ items, const int32_t *__restrict__ lcell,
+             const int32_t *__restrict__ lstart, const uint32_t *__restrict__ off, const uint32_t *__restrict__ cnt,
+             const P2PMeta *__restrict__ meta, const Part64 *__restrict__ parts, int *__restrict__ ctr) {
+    const Pol64<TAB> pol(a.sigma, load_table<double, TAB>(a.table));
+    const int lane = threadIdx.x & 63;
+    for (int k = 0; k < 8; ++k) {
+        const int x = int(blockIdx.x + k) & 7;
+        const int i0 = int(int64_t(nitem) * x / 8), ni = int(int64_t(nitem) * (x + 1) / 8) - i0;
+        for (;;) {
+            int w = 0;
+            if (lane == 0) w = atomicAdd(&ctr[x], 1);
+            w = __builtin_amdgcn_readfirstlane(w);
+            if (w >= ni) break;
+            const int2 it = items[i0 + w];
+            const int c = lcell[it.x];
+            const int s0 = lstart[it.x], end = min(lstart[it.x + 1] - s0, it.y + 64);
+            const uint32_t e0 = off[c], e1 = e0 + cnt[c];
+            for (int base = it.y; base < end;) {
+                const int E = piece_lanes(end - base), b0 = base;
+                base += E;
+                const int t = lane & (E - 1), grp = lane / E, ng = 64 / E;
+                const bool write = b0 + t < end && grp == 0;
+                const int gi = s0 + (b0 + t < end ? b0 + t : b0);
+                const Part64 me = parts[gi];
+                typename Pol64<TAB>::Acc A;
+                Pol64<TAB>::clear(A);
+                // the next entry's record is fetched while the current one's sources are evaluated
+                P2PMeta mn{};
+                if (e1 > e0) mn = meta[e0];
+                for (uint32_t e = e0; e < e1; ++e) {
+                    const P2PMeta m = mn;
+                    mn = meta[e + 1 < e1 ? e + 1 : e];
+                    const double tx = me.dx - m.dx, ty = me.dy - m.dy, tz = me.dz - m.dz;
+                    if (E == 64) pol.uniform(parts, m.js, m.je, tx, ty, tz, A);
+                    else pol.grouped(parts, m.js + grp, m.je, ng, tx, ty, tz, A);
+                }
+                double f[kNearRows];
+                for_rows([&](auto kc) {
+                    constexpr int K = decltype(kc)::value;
+                    f[K] = pol.template value<K>(A);
+                    for (int o = E; o < 64; o <<= 1) f[K] += __shfl_xor(f[K], o);
+                }, std::make_integer_sequence<int, kNearRows>{});
+                finish(a, gi, write, [&](int r) { return f[r]; });
+            }
+        }
+    }
 }
 
 template <typename R>
 using P2PKernel = void (*)(P2PArgs, const R *);
 
 }  // namespace
+
+// workgroups the chip holds at once (80 / 128 registers per lane)
+static int p2p_slots(bool mixed) { return compute_units() * (mixed ? 3 : 2); }
 
 int p2p_shares(int nleaf, int ntarget, bool mixed) {
     const int slots = p2p_slots(mixed);
@@ -1070,7 +686,7 @@ int p2p_shares(int nleaf, int ntarget, bool mixed) {
 // FP32, 1/sigma^2 within the type's range.
 hipError_t launch_p2p64(hipStream_t s, const P2PArgs &a, const Part64 *parts) {
     const bool tab = a.sigma >= 0x1p-100 * a.w;
-    const P2PShape p = p2p_shape(a, false, tab ? PairTab<double>::bytes : 0);
+    const P2PShape p = p2p_shape(a, p2p_slots(false), tab ? PairTab<double>::bytes : 0);
     const P2PKernel<Part64> k = p.split ? (tab ? k_p2p64<true, true> : k_p2p64<true, false>)
                                         : (tab ? k_p2p64<false, true> : k_p2p64<false, false>);
     hipLaunchKernelGGL(k, p.grid, dim3(kP2PThreads), p.smem, s, a, parts);
@@ -1079,7 +695,7 @@ hipError_t launch_p2p64(hipStream_t s, const P2PArgs &a, const Part64 *parts) {
 
 hipError_t launch_p2p32(hipStream_t s, const P2PArgs &a, const Part32 *parts) {
     const bool tab = a.sigma >= 0x1p-20 * a.w && a.sigma >= 0x1p-50 && a.sigma <= 0x1p50;
-    const P2PShape p = p2p_shape(a, true, tab ? PairTab<float>::bytes : 0);
+    const P2PShape p = p2p_shape(a, p2p_slots(true), tab ? PairTab<float>::bytes : 0);
     const P2PKernel<Part32> k = p.split ? (tab ? k_p2p32<true, true> : k_p2p32<true, false>)
                                         : (tab ? k_p2p32<false, true> : k_p2p32<false, false>);
     hipLaunchKernelGGL(k, p.grid, dim3(kP2PThreads), p.smem, s, a, parts);
@@ -1088,10 +704,14 @@ hipError_t launch_p2p32(hipStream_t s, const P2PArgs &a, const Part32 *parts) {
 
 hipError_t launch_p2p64_list(hipStream_t s, const P2PArgs &a, int nitem, const int2 *items, const int32_t *lcell,
                              const int32_t *lstart, const uint32_t *off, const uint32_t *cnt, const P2PMeta *meta,
-                             const Part64 *parts) {
+                             const Part64 *parts, int *ctr) {
     if (nitem == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_p2p64_list, dim3(nitem), dim3(64), 0, s, a, nitem, items, lcell, lstart, off, cnt, meta,
-                       parts);
+    // a.w: the root's width, the largest a leaf can have
+    const bool tab = a.sigma >= 0x1p-100 * a.w;
+    const int wgs = std::min(p2p_slots(false), (nitem + kP2PWaves - 1) / kP2PWaves);
+    hipLaunchKernelGGL(tab ? k_p2p64_list<true> : k_p2p64_list<false>, dim3(unsigned(wgs)), dim3(kP2PThreads),
+                       tab ? PairTab<double>::bytes : 0, s, a, nitem, items, lcell, lstart, off, cnt, meta, parts,
+                       ctr);
     return hipGetLastError();
 }
 

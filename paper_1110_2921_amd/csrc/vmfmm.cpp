@@ -1511,6 +1511,8 @@ vm_status adaptive_impl(vm_ctx *ctx, int64_t n64, const double *x, const double 
     a.scheme = opts->scheme;
     a.have_far = 1;
     a.sigma = sigma;
+    a.w = opts->box_len;
+    a.table = ctx->pair_tab64.ptr;
     a.perm = vin;
     a.alpha = alpha;
     a.far = ctx->far.as<double>();
@@ -1520,10 +1522,10 @@ vm_status adaptive_impl(vm_ctx *ctx, int64_t n64, const double *x, const double 
     {
         Timed tm(ctx, VM_PH_P2P);
         VM_HIP(launch_ad_p2p_meta(s, t, ncell, A.off.as<uint32_t>(), A.cnt.as<uint32_t>(), A.src.as<int32_t>(),
-                                  A.code.as<int8_t>(), A.p2p_meta.as<P2PMeta>()),
+                                  A.code.as<int8_t>(), A.p2p_meta.as<P2PMeta>(), dints + 300),
                "adaptive P2P entries");
         VM_HIP(launch_p2p64_list(s, a, nitem, A.items.as<int2>(), lcell, lstart, A.off.as<uint32_t>(),
-                                 A.cnt.as<uint32_t>(), A.p2p_meta.as<P2PMeta>(), parts),
+                                 A.cnt.as<uint32_t>(), A.p2p_meta.as<P2PMeta>(), parts, dints + 300),
                "adaptive P2P");
     }
     A.valid = true;
