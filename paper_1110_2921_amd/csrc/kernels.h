@@ -214,8 +214,9 @@ struct GaussArgs {
 };
 // Gaussian sums at the targets of the strengths held in the source records' a-fields
 hipError_t launch_gauss(hipStream_t s, const GaussArgs &a, const void *parts, int mixed);
-// records' a-fields <- gamma (sorted order [3][n])
-hipError_t launch_pack(hipStream_t s, int n, const double *gamma, void *parts, int mixed);
+// v <- alpha_c v0 (in place or not) and the records' a-fields <- v (sorted order [3][n])
+hipError_t launch_scale_pack(hipStream_t s, int n, const double *v0, double *v, const double alpha[3], void *parts,
+                             int mixed);
 hipError_t launch_gather3(hipStream_t s, int n, const int32_t *perm, const double *src, double *dst);
 // cell centres of the ng^3 lattice, site (ix ng + iy) ng + iz, [3][ng^3]
 hipError_t launch_lattice_sites(hipStream_t s, int ng, const double lo[3], double h, double *out);
@@ -223,14 +224,20 @@ hipError_t launch_scatter3(hipStream_t s, int n, const int32_t *perm, const doub
 
 constexpr int kRbfDotBlocks = 512;
 constexpr int kRbfMaxVecs = 32;
+constexpr int kRbfMaxDots = 20;   // vectors of a Gram-Schmidt pass
 struct RbfCoefs {
     double alpha[3];
     double c[3 * kRbfMaxVecs];   // c[3 j + component]
 };
-// out[3 j + c] = <w_c, v_{j,c}>, j < k <= kRbfMaxVecs, v_j = V + j ldv, fixed
-// reduction order; `partial` holds 3 k kRbfDotBlocks doubles
-hipError_t launch_multidot(hipStream_t s, int n, const double *w, const double *V, int64_t ldv, int k,
-                           double *partial, double *out);
+// Classical Gram-Schmidt, twice, of w against v_j = V + j ldv, j < k <= kRbfMaxDots,
+// for the components in `active` (the others stay).  host[3 j + c], host[3 (k + j)
+// + c]: the two passes' dot products, host[6 k + c]: <w_c, w_c> after them.
+// `partial`: 6 kRbfMaxVecs kRbfDotBlocks doubles, h: 6 kRbfMaxDots; host: memory that
+// the host reads after a synchronization.  Fixed reduction order.
+hipError_t launch_orthogonalize(hipStream_t s, int n, double *w, const double *V, int64_t ldv, int k, int active,
+                                double *partial, double *h, double *host);
+// r <- b - r; host[c] = <r_c, r_c>
+hipError_t launch_residual(hipStream_t s, int n, const double *b, double *r, double *partial, double *host);
 // w_c <- alpha_c w_c + sum_{j < k} c_{j,c} v_{j,c}
 hipError_t launch_multiaxpy(hipStream_t s, int n, double *w, const double *V, int64_t ldv, int k,
                             const RbfCoefs &c);

@@ -134,6 +134,7 @@ struct vm_ctx {
     DevBuf rk_u, rk_s, rk_x, rk_a, diag;
     DevBuf adj_u, adj_J, adj_v, adj_Jv, adj_far, adj_p64, adj_p32;
     DevBuf rbf_b, rbf_x, rbf_V, rbf_part, rbf_dots;   // RBF solve: right side, iterate, Krylov basis, reductions
+    double *rbf_host = nullptr;   // pinned: the reductions that the host reads, [6 kRbfMaxDots + 3]
     // second tree over a distinct target set (Gaussian sums at other points)
     DevBuf t_keys_a, t_keys_b, t_vals_a, t_vals_b, t_start, t_p64, t_p32;
     DevBuf rin_y, rin_w, run_J;   // reinitialisation: lattice sites, vorticity there; loop: gradient
@@ -1593,6 +1594,7 @@ void vm_destroy(vm_ctx *ctx) {
     if (ctx->ev_join) (void)hipEventDestroy(ctx->ev_join);
     for (hipEvent_t e : ctx->events) (void)hipEventDestroy(e);
     if (ctx->fft_ng > 0) (void)hipfftDestroy(ctx->fft_plan);
+    if (ctx->rbf_host) (void)hipHostFree(ctx->rbf_host);
     delete ctx;
 }
 
@@ -1964,7 +1966,8 @@ vm_status vm_gauss_eval(vm_ctx *ctx, int64_t n, const double *x, const double *g
     return check_flag(ctx, opts);
 }
 
-static_assert(VM_RBF_RESTART + 1 <= kRbfMaxVecs, "Krylov basis exceeds the multi-vector kernels");
+static_assert(VM_RBF_RESTART + 1 <= kRbfMaxVecs && VM_RBF_RESTART <= kRbfMaxDots,
+              "Krylov basis exceeds the multi-vector kernels");
 
 vm_status vm_rbf_solve(vm_ctx *ctx, int64_t n, const double *x, const double *omega, double sigma, double h3,
                        int level, const vm_opts *opts, double tol, int max_iter, double *gamma, int *iters,
@@ -1986,8 +1989,13 @@ vm_status vm_rbf_solve(vm_ctx *ctx, int64_t n, const double *x, const double *om
     VM_HIP(ctx->rbf_b.reserve(sizeof(double) * vlen), "alloc rbf");
     VM_HIP(ctx->rbf_x.reserve(sizeof(double) * vlen), "alloc rbf");
     VM_HIP(ctx->rbf_V.reserve(sizeof(double) * vlen * (m + 1)), "alloc rbf basis");
-    VM_HIP(ctx->rbf_part.reserve(sizeof(double) * 3 * kRbfMaxVecs * kRbfDotBlocks), "alloc rbf");
-    VM_HIP(ctx->rbf_dots.reserve(sizeof(double) * 3 * kRbfMaxVecs), "alloc rbf");
+    VM_HIP(ctx->rbf_part.reserve(sizeof(double) * 6 * kRbfMaxVecs * kRbfDotBlocks), "alloc rbf");
+    VM_HIP(ctx->rbf_dots.reserve(sizeof(double) * 6 * kRbfMaxDots), "alloc rbf");
+    if (!ctx->rbf_host) {
+        void *p = nullptr;
+        VM_HIP(hipHostMalloc(&p, sizeof(double) * (6 * kRbfMaxDots + 3), hipHostMallocDefault), "alloc rbf");
+        ctx->rbf_host = static_cast<double *>(p);
+    }
     TreeGeom g;
     int32_t *perm = nullptr;
     void *parts = nullptr;
@@ -2010,23 +2018,17 @@ vm_status vm_rbf_solve(vm_ctx *ctx, int64_t n, const double *x, const double *om
     ga.start = ctx->start.as<int32_t>();
     ga.tstart = ga.start;
     ga.tparts = parts;
-    auto matvec = [&](const double *v, double *out) -> vm_status {
+    // v <- alpha v0, out <- A v
+    auto matvec = [&](const double *v0, const double alpha[3], double *v, double *out) -> vm_status {
         Timed tm(ctx, VM_PH_GAUSS);
-        VM_HIP(launch_pack(s, ni, v, parts, mixed), "pack strengths");
+        VM_HIP(launch_scale_pack(s, ni, v0, v, alpha, parts, mixed), "pack strengths");
         ga.out = out;
         VM_HIP(launch_gauss(s, ga, parts, mixed), "gaussian sum");
         return VM_OK;
     };
-    std::vector<double> dots(3 * kRbfMaxVecs);
-    // dots[3 j + c] = <w_c, v_{j,c}>, j < k (synchronises)
-    auto multidot = [&](const double *w, const double *Vb, int k) -> vm_status {
-        {
-            Timed tm(ctx, VM_PH_KRYLOV);
-            VM_HIP(launch_multidot(s, ni, w, Vb, ldv, k, ctx->rbf_part.as<double>(), ctx->rbf_dots.as<double>()),
-                   "dot products");
-        }
-        VM_HIP(hipMemcpyAsync(dots.data(), ctx->rbf_dots.ptr, sizeof(double) * 3 * k, hipMemcpyDeviceToHost, s),
-               "read dot products");
+    double *part = ctx->rbf_part.as<double>();
+    const double *dots = ctx->rbf_host;   // valid after read()
+    auto read = [&]() -> vm_status {
         VM_HIP(hipStreamSynchronize(s), "synchronize");
         return VM_OK;
     };
@@ -2043,11 +2045,7 @@ vm_status vm_rbf_solve(vm_ctx *ctx, int64_t n, const double *x, const double *om
     {
         Timed tm(ctx, VM_PH_KRYLOV);
         VM_HIP(launch_gather3(s, ni, perm, omega, b), "gather");
-        VM_HIP(hipMemcpyAsync(xs, b, sizeof(double) * vlen, hipMemcpyDeviceToDevice, s), "copy");
     }
-    clear();
-    for (int c = 0; c < 3; ++c) cf.alpha[c] = h3;
-    if ((st = axpy(xs, V, 0, cf)) != VM_OK) return st;
 
     // GMRES(m) on each component's system A gamma_c = omega_c, the three run
     // in lockstep so that every product serves all of them
@@ -2062,16 +2060,16 @@ vm_status vm_rbf_solve(vm_ctx *ctx, int64_t n, const double *x, const double *om
     double beta0[3] = {0, 0, 0}, rel[3] = {0, 0, 0};
     bool done[3] = {false, false, false};
     int total = 0;
+    const double one[3] = {1.0, 1.0, 1.0}, first[3] = {h3, h3, h3};
+    double alpha[3];   // of the last basis vector, applied by the next product
     for (int cycle = 0;; ++cycle) {
         // r = omega - A gamma into v_0
-        if ((st = matvec(xs, vec(0))) != VM_OK) return st;
-        clear();
-        for (int c = 0; c < 3; ++c) {
-            cf.alpha[c] = -1.0;
-            cf.c[c] = 1.0;
+        if ((st = cycle == 0 ? matvec(b, first, xs, vec(0)) : matvec(xs, one, xs, vec(0))) != VM_OK) return st;
+        {
+            Timed tm(ctx, VM_PH_KRYLOV);
+            VM_HIP(launch_residual(s, ni, b, vec(0), part, ctx->rbf_host), "residual");
         }
-        if ((st = axpy(vec(0), b, 1, cf)) != VM_OK) return st;
-        if ((st = multidot(vec(0), vec(0), 1)) != VM_OK) return st;
+        if ((st = read()) != VM_OK) return st;
         double beta[3];
         for (int c = 0; c < 3; ++c) {
             beta[c] = std::sqrt(dots[c]);
@@ -2085,39 +2083,31 @@ vm_status vm_rbf_solve(vm_ctx *ctx, int64_t n, const double *x, const double *om
         if ((done[0] && done[1] && done[2]) || total >= max_iter) break;
         bool active[3];
         int cols[3] = {0, 0, 0};
-        clear();
         for (int c = 0; c < 3; ++c) {
             active[c] = !done[c];
-            cf.alpha[c] = active[c] ? 1.0 / beta[c] : 0.0;
+            alpha[c] = active[c] ? 1.0 / beta[c] : 0.0;
             std::fill(gv[c].begin(), gv[c].end(), 0.0);
             gv[c][0] = beta[c];
         }
-        if ((st = axpy(vec(0), V, 0, cf)) != VM_OK) return st;
         for (int j = 0; j < m && total < max_iter && (active[0] || active[1] || active[2]); ++j) {
             double *w = vec(j + 1);
-            if ((st = matvec(vec(j), w)) != VM_OK) return st;
+            if ((st = matvec(vec(j), alpha, vec(j), w)) != VM_OK) return st;
             ++total;
             // classical Gram-Schmidt, twice
-            std::vector<double> h(3 * size_t(j + 1), 0.0);
-            for (int pass = 0; pass < 2; ++pass) {
-                if ((st = multidot(w, V, j + 1)) != VM_OK) return st;
-                clear();
-                for (int c = 0; c < 3; ++c) cf.alpha[c] = 1.0;
-                for (int i = 0; i <= j; ++i)
-                    for (int c = 0; c < 3; ++c)
-                        if (active[c]) {
-                            h[3 * i + c] += dots[3 * i + c];
-                            cf.c[3 * i + c] = -dots[3 * i + c];
-                        }
-                if ((st = axpy(w, V, j + 1, cf)) != VM_OK) return st;
+            const int k = j + 1, mask = int(active[0]) | int(active[1]) << 1 | int(active[2]) << 2;
+            {
+                Timed tm(ctx, VM_PH_KRYLOV);
+                VM_HIP(launch_orthogonalize(s, ni, w, V, ldv, k, mask, part, ctx->rbf_dots.as<double>(),
+                                            ctx->rbf_host),
+                       "orthogonalization");
             }
-            if ((st = multidot(w, w, 1)) != VM_OK) return st;
-            clear();
+            if ((st = read()) != VM_OK) return st;
             for (int c = 0; c < 3; ++c) {
+                alpha[c] = 0.0;
                 if (!active[c]) continue;
-                const double nrm = std::sqrt(dots[c]);
+                const double nrm = std::sqrt(dots[6 * k + c]);
                 double *col = &H[c][size_t(j) * ld];
-                for (int i = 0; i <= j; ++i) col[i] = h[3 * i + c];
+                for (int i = 0; i <= j; ++i) col[i] = dots[3 * i + c] + dots[3 * (k + i) + c];
                 col[j + 1] = nrm;
                 for (int i = 0; i < j; ++i) {
                     const double t = cs[c][i] * col[i] + sn[c][i] * col[i + 1];
@@ -2135,9 +2125,8 @@ vm_status vm_rbf_solve(vm_ctx *ctx, int64_t n, const double *x, const double *om
                 rel[c] = std::fabs(gv[c][j + 1]) / beta0[c];
                 if (rel[c] <= tol) done[c] = true;
                 if (done[c] || !(nrm > 0.0)) active[c] = false;
-                cf.alpha[c] = active[c] ? 1.0 / nrm : 0.0;
+                alpha[c] = active[c] ? 1.0 / nrm : 0.0;
             }
-            if ((st = axpy(w, V, 0, cf)) != VM_OK) return st;
         }
         // gamma += V y for each component
         clear();
