@@ -74,16 +74,17 @@ __device__ __forceinline__ void centre(const AdTreeView &t, int c, double out[3]
 }
 
 // sort key of each cell for the octant groups of all levels at once:
-// level * 8 + octant (a stable sort keeps the key order inside a group)
-__global__ void __launch_bounds__(256) k_ad_group_keys(AdTreeView t, int ncell, uint32_t *__restrict__ keys,
+// octant * nlev + level (a stable sort keeps the key order inside a group; an
+// octant's cells of all levels are contiguous)
+__global__ void __launch_bounds__(256) k_ad_group_keys(AdTreeView t, int ncell, int nlev, uint32_t *__restrict__ keys,
                                                        int32_t *__restrict__ idx) {
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= ncell) return;
-    keys[c] = uint32_t(t.level[c]) * 8u + (t.key[c] & 7u);
+    keys[c] = (t.key[c] & 7u) * uint32_t(nlev) + uint32_t(t.level[c]);
     idx[c] = c;
 }
 
-// the first position of each (level, octant) group, from the sort pass's
+// the first position of each (octant, level) group, from the sort pass's
 // scanned histogram (digit-major, block 0 first), and the cell count
 __global__ void k_ad_group_starts(int ngroup, int nblk, int ncell, const uint32_t *__restrict__ offs,
                                   int *__restrict__ starts) {
@@ -439,7 +440,7 @@ __global__ void __launch_bounds__(64) k_ad_traverse(AdTreeView t, AdLists ls, in
 // conjugated irregular harmonics of source particle j (relative to the target
 // centre, in target widths) into its LDS row; lanes then sum the rows per
 // coefficient, weighted by the particles' strengths, and add the result to the
-// cell's local expansion (which already holds L2L and M2L).
+// cell's local expansion (which already holds its M2L).
 __global__ void __launch_bounds__(64) k_ad_p2l(AdTreeView t, AdLists ls, int off, int ncl, int ncell, int p, int kp,
                                                DevTables tab, const Part64 *__restrict__ parts,
                                                double *__restrict__ L) {
@@ -716,7 +717,7 @@ inline int blocks(int n, int t) { return (n + t - 1) / t; }
 hipError_t launch_ad_groups(hipStream_t s, const AdTreeView &t, int ncell, int nlev, uint32_t *ka, int32_t *va,
                             uint32_t *kb, int32_t *vb, uint32_t *hist, int *starts) {
     if (ncell == 0 || nlev * 8 > 256) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_ad_group_keys, dim3(blocks(ncell, 256)), dim3(256), 0, s, t, ncell, ka, va);
+    hipLaunchKernelGGL(k_ad_group_keys, dim3(blocks(ncell, 256)), dim3(256), 0, s, t, ncell, nlev, ka, va);
     int bits = 0;
     while ((1 << bits) < nlev * 8) ++bits;
     hipError_t e = launch_radix_pass(s, ncell, 0, bits, ka, va, kb, vb, hist);

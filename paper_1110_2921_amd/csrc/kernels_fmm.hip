@@ -472,19 +472,17 @@ __global__ void __launch_bounds__(kTrThreads) k_translate(int level, int periodi
 
     int octant = 0, tile = blockIdx.x, npair = 1, pr0 = 0;
     int64_t ncell_t;
-    const bool adaptive = ad.tcell != nullptr;   // cells and sources from tables (adaptive tree)
+    const bool adaptive = mode == 0 && ad.tcell != nullptr;   // cells and sources from tables (adaptive tree)
     if (mode == 2) {                  // M2M: targets are the parents at `level`
-        ncell_t = adaptive ? ad.ntarget : int64_t(1) << (3 * level);
+        ncell_t = int64_t(1) << (3 * level);
         npair = 8;
-    } else if (adaptive) {            // octant groups of one level, tile_start[o] .. workgroups each
+    } else if (adaptive) {            // M2L, octant groups, tile_start[o] .. workgroups each
         octant = 0;
         while (octant < 7 && int(blockIdx.x) >= ad.tile_start[octant + 1]) ++octant;
         tile = int(blockIdx.x) - ad.tile_start[octant];
         ncell_t = ad.oct_n[octant];
-        if (mode == 0) {
-            pr0 = int(blockIdx.y) * 189 / nsplit;
-            npair = (int(blockIdx.y) + 1) * 189 / nsplit - pr0;
-        }
+        pr0 = int(blockIdx.y) * 189 / nsplit;
+        npair = (int(blockIdx.y) + 1) * 189 / nsplit - pr0;
     } else {                          // M2L / L2L: targets at `level`, grouped by octant
         octant = blockIdx.x & 7;
         tile = blockIdx.x >> 3;
@@ -498,12 +496,7 @@ __global__ void __launch_bounds__(kTrThreads) k_translate(int level, int periodi
         const int64_t slot = int64_t(tile) * TTN + tid;
         int32_t k = -1;
         if (adaptive) {
-            if (slot < ncell_t) k = mode == 2 ? ad.tcell[slot] : ad.tcell[ad.oct_base[octant] + slot];
-            if (mode == 2 && k >= 0) {
-                bool any = false;
-                for (int o = 0; o < 8; ++o) any = any || ad.child[8 * size_t(k) + o] >= 0;
-                if (!any) k = -1;     // a leaf: its multipole is its own P2M
-            }
+            if (slot < ncell_t) k = ad.tcell[ad.oct_base[octant] + slot];
         } else if (slot < ncell_t) {
             k = mode == 2 ? int32_t(slot) : int32_t((slot << 3) | octant);
         }
@@ -522,11 +515,7 @@ __global__ void __launch_bounds__(kTrThreads) k_translate(int level, int periodi
     auto source_key = [&](int i) -> int32_t {
         const int32_t t = tkey[tid];
         if (t < 0) return -1;
-        if (adaptive) {
-            if (mode == 0) return ad.stab[size_t(t - ad.cell0) * 189 + pr0 + i];
-            if (mode == 1) return ad.parent[t];
-            return ad.child[8 * size_t(t) + i];
-        }
+        if (adaptive) return ad.stab[size_t(t - ad.cell0) * 189 + pr0 + i];
         if (mode == 0) {
             const int op = op_of(i);
             int c[3];
@@ -704,7 +693,11 @@ __global__ void __launch_bounds__(256) k_split_reduce(int64_t nelem, int kp, int
 // operand straight from L2 into the MFMA's registers, four k blocks in flight:
 // M2M 4 to 6 us a level (13 us for 512 parents in FP64), L2L 4 to 8 (14 to 20
 // before).  An operator is read once per 16 columns: at 4096 parents (768 column
-// tiles) still as fast as k_translate, which the finer levels keep.
+// tiles) still as fast as k_translate, which the finer levels keep.  The adaptive
+// tree takes these kernels at every level: half its parents are leaves, whose
+// columns stop at once, and an octant's group ends in a 16-column tile instead of
+// a 16-cell one (2^21 clustered particles, p = 10: 28.2 ms an evaluation, 28.7
+// with k_translate beyond 4096 cells; 2^20 with leaves of 20: 33.0 and 33.8).
 constexpr int kTrCoarseCells = 4096;   // M2M parents, L2L targets
 
 template <typename T>
@@ -733,48 +726,68 @@ __device__ __forceinline__ typename Mfma<T>::v4 tr_column_product(const T *__res
     return acc;
 }
 
-// grid (column tiles of the parents, row blocks)
-template <typename T>
+// grid (column tiles of the parents, row blocks); AD: parents and children from the
+// adaptive tree's tables (a parent without children keeps its own P2M)
+template <typename T, bool AD>
 __global__ void __launch_bounds__(kTrThreads) k_m2m_coarse(int ncell, int C, int kp, int nrb, int nkb,
                                                            const T *__restrict__ ops, const T *__restrict__ src,
-                                                           T *__restrict__ dst) {
+                                                           T *__restrict__ dst, AdaptTr ad) {
     __shared__ T red[kTrWaves * 256];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rb = blockIdx.y, j = int(blockIdx.x) * 16 + (lane & 15);
     const int cell = j / 3 < ncell ? j / 3 : 0, comp = j % 3;
     const T *op = ops + (size_t(wave) * nrb + rb) * nkb * 256 + 4 * lane;
-    const T *sp = src + ((size_t(cell) * 8 + wave) * 3 + comp) * kp + 4 * (lane >> 4);
+    const int child = AD ? (j / 3 < ncell ? ad.child[8 * size_t(ad.tcell[cell]) + wave] : -1) : 8 * cell + wave;
+    const T *sp = src + (size_t(child < 0 ? 0 : child) * 3 + comp) * kp + 4 * (lane >> 4);
     typename Mfma<T>::v4 acc{T(0), T(0), T(0), T(0)};
-    acc = tr_column_product<T>(op, sp, nkb, acc);
+    if (!AD || __any(child >= 0)) acc = tr_column_product<T>(op, sp, nkb, acc);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) red[wave * 256 + lane * 4 + r] = acc[r];
+    for (int r = 0; r < 4; ++r) red[wave * 256 + lane * 4 + r] = child < 0 ? T(0) : acc[r];   // a column a lane
     __syncthreads();
     if (tid >= 256) return;
     T x = T(0);
 #pragma unroll
     for (int w = 0; w < kTrWaves; ++w) x += red[w * 256 + tid];
     const int l = tid >> 2, row = rb * 16 + Mfma<T>::row(l, tid & 3), jl = int(blockIdx.x) * 16 + (l & 15);
-    if (jl / 3 < ncell && row < C) dst[(size_t(jl / 3) * 3 + jl % 3) * kp + row] = x;
+    if (jl / 3 >= ncell || row >= C) return;
+    size_t out = jl / 3;
+    if constexpr (AD) {
+        out = ad.tcell[jl / 3];
+        bool any = false;
+#pragma unroll
+        for (int o = 0; o < 8; ++o) any = any || ad.child[8 * out + o] >= 0;
+        if (!any) return;
+    }
+    dst[(out * 3 + jl % 3) * kp + row] = x;
 }
 
 // grid (8 octants x column tiles of an octant's targets, groups of 8 row blocks)
-template <typename T>
+template <typename T, bool AD>
 __global__ void __launch_bounds__(kTrThreads) k_l2l_coarse(int ncell, int C, int kp, int nrb, int nkb,
                                                            const T *__restrict__ ops, const T *__restrict__ src,
-                                                           T *__restrict__ dst, int accumulate) {
+                                                           T *__restrict__ dst, int accumulate, AdaptTr ad) {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
     const int rb = int(blockIdx.y) * kTrWaves + wave, octant = blockIdx.x & 7;
     if (rb * 16 >= C) return;
     const int j = int(blockIdx.x >> 3) * 16 + (lane & 15);
     const int slot = j / 3, comp = j % 3;
+    if constexpr (AD) {
+        ncell = ad.oct_n[octant];
+        if (int(blockIdx.x >> 3) * 16 >= 3 * ncell) return;
+    }
     const T *op = ops + (size_t(octant) * nrb + rb) * nkb * 256 + 4 * lane;
-    const T *sp = src + (size_t(slot < ncell ? slot : 0) * 3 + comp) * kp + 4 * (lane >> 4);
+    size_t target = size_t(slot) * 8 + octant, parent = slot < ncell ? slot : 0;
+    if constexpr (AD) {
+        target = ad.tcell[ad.oct_base[octant] + (slot < ncell ? slot : 0)];
+        parent = ad.parent[target];
+    }
+    const T *sp = src + (parent * 3 + comp) * kp + 4 * (lane >> 4);
     typename Mfma<T>::v4 acc{T(0), T(0), T(0), T(0)};
     acc = tr_column_product<T>(op, sp, nkb, acc);
     if (slot >= ncell) return;
-    T *out = dst + ((size_t(slot) * 8 + octant) * 3 + comp) * kp;
+    T *out = dst + (target * 3 + comp) * kp;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int row = rb * 16 + Mfma<T>::row(lane, r);
@@ -1145,14 +1158,15 @@ hipError_t launch_translate(hipStream_t s, int mode, int level, int periodic, in
     const int nrbw = nrb / kTrWaves;
     if (mode == 2 && (int64_t(1) << (3 * level)) <= kTrCoarseCells) {
         const int n = 1 << (3 * level);
-        hipLaunchKernelGGL(k_m2m_coarse<T>, dim3(unsigned((3 * n + 15) / 16), unsigned((C + 15) / 16)),
-                           dim3(kTrThreads), 0, s, n, C, kp, nrb, tr_nks(C) / 4, ops, src, dst);
+        hipLaunchKernelGGL((k_m2m_coarse<T, false>), dim3(unsigned((3 * n + 15) / 16), unsigned((C + 15) / 16)),
+                           dim3(kTrThreads), 0, s, n, C, kp, nrb, tr_nks(C) / 4, ops, src, dst, AdaptTr());
         return hipGetLastError();
     }
     if (mode == 1 && (int64_t(1) << (3 * level)) <= kTrCoarseCells) {
         const int n = 1 << (3 * (level - 1));
-        hipLaunchKernelGGL(k_l2l_coarse<T>, dim3(unsigned((3 * n + 15) / 16 * 8), unsigned(nrbw)), dim3(kTrThreads),
-                           0, s, n, C, kp, nrb, tr_nks(C) / 4, ops, src, dst, accumulate);
+        hipLaunchKernelGGL((k_l2l_coarse<T, false>), dim3(unsigned((3 * n + 15) / 16 * 8), unsigned(nrbw)),
+                           dim3(kTrThreads), 0, s, n, C, kp, nrb, tr_nks(C) / 4, ops, src, dst, accumulate,
+                           AdaptTr());
         return hipGetLastError();
     }
     const TrShape sh = translate_shape<T>(kp);
@@ -1250,20 +1264,29 @@ hipError_t launch_translate_adaptive(hipStream_t s, int mode, int p, int kp, con
     const int C = (p + 1) * (p + 1);
     const int nrb = tr_nrb(C);
     const int nrbw = nrb / kTrWaves;
+    if (mode == 2) {
+        if (ad.ntarget == 0) return hipSuccess;
+        hipLaunchKernelGGL((k_m2m_coarse<T, true>), dim3(unsigned((3 * ad.ntarget + 15) / 16), unsigned((C + 15) / 16)),
+                           dim3(kTrThreads), 0, s, ad.ntarget, C, kp, nrb, tr_nks(C) / 4, ops, src, dst, ad);
+        return hipGetLastError();
+    }
+    if (mode == 1) {
+        int n = 0;
+        for (int o = 0; o < 8; ++o) n = std::max(n, ad.oct_n[o]);
+        if (n == 0) return hipSuccess;
+        hipLaunchKernelGGL((k_l2l_coarse<T, true>), dim3(unsigned((3 * n + 15) / 16 * 8), unsigned(nrbw)),
+                           dim3(kTrThreads), 0, s, n, C, kp, nrb, tr_nks(C) / 4, ops, src, dst, accumulate, ad);
+        return hipGetLastError();
+    }
     const TrShape sh = translate_shape<T>(kp);
     const int ttn = 16 * sh.nt;
     AdaptTr a = ad;
-    int grid;
-    if (mode == 2) {
-        grid = (a.ntarget + ttn - 1) / ttn;
-    } else {
-        a.tile_start[0] = 0;
-        for (int o = 0; o < 8; ++o) a.tile_start[o + 1] = a.tile_start[o] + (a.oct_n[o] + ttn - 1) / ttn;
-        grid = a.tile_start[8];
-    }
+    a.tile_start[0] = 0;
+    for (int o = 0; o < 8; ++o) a.tile_start[o + 1] = a.tile_start[o] + (a.oct_n[o] + ttn - 1) / ttn;
+    const int grid = a.tile_start[8];
     if (grid == 0) return hipSuccess;
     int nsplit = 1;
-    if (mode == 0 && part != nullptr && a.part_cells > 0 && grid < kTrFillWorkgroups) {
+    if (part != nullptr && a.part_cells > 0 && grid < kTrFillWorkgroups) {
         nsplit = (kTrFillWorkgroups + grid - 1) / grid;
         if (nsplit > 189) nsplit = 189;
         const size_t per_split = size_t(a.part_cells) * 3 * kp;

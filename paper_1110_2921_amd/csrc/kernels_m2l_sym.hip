@@ -277,7 +277,7 @@ __global__ void __launch_bounds__(kSymThreads) k_m2l_sym(int level, int periodic
 // right after its MFMAs.  Blocks are stored as [half][lane group][row][2].
 constexpr int kRing = 8;
 
-// AD: the targets and sources of an adaptive tree's level (SymAdapt) instead
+// AD: the targets and sources of an adaptive tree, all levels (SymAdapt), instead
 // of a uniform level's cells.
 template <int P, bool AD>
 __global__ void __launch_bounds__(kSymThreads) k_m2l_sym64(int level, int periodic, int kp,
