@@ -37,9 +37,12 @@ using dev::irregular_packed;
 using dev::irregular_packed_orders;
 
 __device__ __forceinline__ int ad_coord(uint32_t k, int d, int level) {
-    int c = 0;
-    for (int b = 0; b < level; ++b) c |= int((k >> (3 * b + d)) & 1u) << b;
-    return c;
+    uint32_t x = (k >> d) & 0x09249249u;
+    x = (x | (x >> 2)) & 0x030c30c3u;
+    x = (x | (x >> 4)) & 0x0300f00fu;
+    x = (x | (x >> 8)) & 0x030000ffu;
+    x = (x | (x >> 16)) & 0x000003ffu;
+    return int(x & ((1u << level) - 1u));
 }
 
 __device__ __forceinline__ bool ad_leaf(const AdTreeView &t, int c) {
@@ -51,16 +54,19 @@ __device__ __forceinline__ int shift_of(int code, int d) {
     return d == 0 ? code % 3 - 1 : (d == 1 ? (code / 3) % 3 - 1 : code / 9 - 1);
 }
 
-// Do the closed cubes of a and of b shifted by image `code` touch?
-__device__ __forceinline__ bool touching(const AdTreeView &t, int a, int b, int code) {
-    const int la = t.level[a], lb = t.level[b], M = t.max_level;
+// Do the closed cubes of cell ca at level la and of the cell with key kb at level
+// lb, shifted by image `code`, touch?
+__device__ __forceinline__ bool touching(const AdTreeView &t, const int ca[3], int la, uint32_t kb, int lb, int code) {
+    const int M = t.max_level;
     const int na = 1 << (M - la), nb = 1 << (M - lb);
+    bool yes = true;
+#pragma unroll
     for (int d = 0; d < 3; ++d) {
-        const int ca = ad_coord(t.key[a], d, la) << (M - la);
-        const int cb = (ad_coord(t.key[b], d, lb) << (M - lb)) + shift_of(code, d) * (1 << M);
-        if (ca > cb + nb || cb > ca + na) return false;
+        const int a = ca[d] << (M - la);
+        const int b = (ad_coord(kb, d, lb) << (M - lb)) + shift_of(code, d) * (1 << M);
+        yes = yes && a <= b + nb && b <= a + na;
     }
-    return true;
+    return yes;
 }
 
 __device__ __forceinline__ void centre(const AdTreeView &t, int c, double out[3]) {
@@ -323,7 +329,7 @@ __global__ void __launch_bounds__(64) k_ad_traverse(AdTreeView t, AdLists ls, in
         // apart: cell-cell between cells of one level; particle-cell from a
         // coarser leaf b only into a split cell a -- a leaf a takes b's
         // particles directly, the cheaper of the two for cells of <= ncrit
-        if (!touching(t, a, b, code) && (lb == l || !leaf_a)) {
+        if (!touching(t, ca, l, t.key[b], lb, code) && (lb == l || !leaf_a)) {
             if (lb == l) {
                 if (write) {
                     int idx = 0, mul = 1;
@@ -348,31 +354,41 @@ __global__ void __launch_bounds__(64) k_ad_traverse(AdTreeView t, AdLists ls, in
             put(0, b);
         } else if (leaf_a) {
             // walk b's subtree: split cells apart from a are M2P sources,
-            // its leaves (apart or touching) P2P sources
+            // its leaves (apart or touching) P2P sources.  A step takes the
+            // eight children of a split cell, their records fetched together:
+            // the walk is a chain of loads (filling pass of 20011 periodic
+            // particles 147 us with a cell a step and coordinates bit by bit,
+            // now 46; 2^19 free 195, now 82).
             int sp = 0;
-            for (int o = 0; o < 8; ++o) {
-                const int e = t.child[8 * b + o];
-                if (e >= 0) {
-                    if (sp < kAdStack) stack[sp++] = e;
-                    else bad = true;
+            for (int e = b; e >= 0;) {
+                const int le = t.level[e] + 1;
+                const int4 *cp = reinterpret_cast<const int4 *>(t.child + 8 * size_t(e));
+                const int4 c0 = cp[0], c1 = cp[1];
+                const int ch[8] = {c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w};
+                uint32_t key[8];
+                int count[8];
+#pragma unroll
+                for (int o = 0; o < 8; ++o) {
+                    key[o] = t.key[ch[o] < 0 ? 0 : ch[o]];
+                    count[o] = t.count[ch[o] < 0 ? 0 : ch[o]];
                 }
-            }
-            while (sp > 0) {
-                const int e = stack[--sp];
-                const bool leaf_e = ad_leaf(t, e);
-                if (!leaf_e && !touching(t, a, e, code)) {
-                    put(1, e);   // M2P from a split cell only
-                } else if (leaf_e) {
-                    put(0, e);
-                } else {
-                    for (int o = 0; o < 8; ++o) {
-                        const int f = t.child[8 * e + o];
-                        if (f >= 0) {
-                            if (sp < kAdStack) stack[sp++] = f;
+                int next = -1;
+#pragma unroll
+                for (int o = 0; o < 8; ++o) {
+                    if (ch[o] < 0) continue;
+                    if (count[o] <= t.ncrit || le >= t.max_level) {
+                        put(0, ch[o]);
+                    } else if (!touching(t, ca, l, key[o], le, code)) {
+                        put(1, ch[o]);   // M2P from a split cell only
+                    } else {
+                        if (next >= 0) {
+                            if (sp < kAdStack) stack[sp++] = next;
                             else bad = true;
                         }
+                        next = ch[o];
                     }
                 }
+                e = next >= 0 ? next : (sp > 0 ? stack[--sp] : -1);
             }
         } else {
             partner = true;     // a is split: the pair goes to a's children
