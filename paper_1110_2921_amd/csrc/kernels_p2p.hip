@@ -612,32 +612,40 @@ k_p2p32(P2PArgs a, const Part32 *__restrict__ parts) {
 // order, first target of the block of up to 64 within the leaf), its sources the
 // leaf's P2P list: entry (source range, D = centre_b + s L - centre_a) contributes
 // x_i - x_j - s L = (delta_i - D) - delta_j, the records relative to their own
-// leaf centres.  A wave per item; the 8 waves of a workgroup share the pair table.
-// Items differ by a factor of ten in work and a workgroup's table and registers
-// hold half a compute unit, so the workgroups are as many as fit and their waves
+// leaf centres.  Items differ by a factor of ten in work and a workgroup's table
+// and registers hold half a compute unit, so the workgroups are as many as fit and
 // take items one by one, first from their XCD's contiguous eighth (neighbour
 // leaves share its L2), then from the others' (ctr[8]: items taken of each eighth,
-// zero at the start).  P2P of 2^19 clustered particles 2.05 ms
-// (pair function by polynomials, one wave per workgroup and item: 3.83 ms).
+// zero at the start).  Wave w takes entries w, w + 8, ... of the item's list, the
+// waves' sums added in wave order: a wave per item ended with the longest item
+// (20011 particles in leaves of 32: 400 us, the evaluation 1.64 ms, now 1.36; 2^17
+// in leaves of 64 4.09 and 3.58; 2^19 no difference).  P2P of 2^19 clustered
+// particles 2.05 ms (pair function by polynomials: 3.83 ms).
 template <bool TAB>
 __global__ void __launch_bounds__(kP2PThreads) __attribute__((amdgpu_waves_per_eu(TAB ? 4 : 2, TAB ? 4 : 2)))
 k_p2p64_list(P2PArgs a, int nitem, const int2 *__restrict__ items, const int32_t *__restrict__ lcell,
              const int32_t *__restrict__ lstart, const uint32_t *__restrict__ off, const uint32_t *__restrict__ cnt,
              const P2PMeta *__restrict__ meta, const Part64 *__restrict__ parts, int *__restrict__ ctr) {
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    __shared__ int taken;
     const Pol64<TAB> pol(a.sigma, load_table<double, TAB>(a.table));
-    const int lane = threadIdx.x & 63;
+    double *red = reinterpret_cast<double *>(smem_raw + (TAB ? PairTab<double>::bytes : 0));
+    double *fin = red + kRedRows * kP2PThreads;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     for (int k = 0; k < 8; ++k) {
         const int x = int(blockIdx.x + k) & 7;
         const int i0 = int(int64_t(nitem) * x / 8), ni = int(int64_t(nitem) * (x + 1) / 8) - i0;
         for (;;) {
-            int w = 0;
-            if (lane == 0) w = atomicAdd(&ctr[x], 1);
-            w = __builtin_amdgcn_readfirstlane(w);
+            if (tid == 0) taken = atomicAdd(&ctr[x], 1);
+            __syncthreads();
+            const int w = __builtin_amdgcn_readfirstlane(taken);
+            __syncthreads();
             if (w >= ni) break;
             const int2 it = items[i0 + w];
             const int c = lcell[it.x];
             const int s0 = lstart[it.x], end = min(lstart[it.x + 1] - s0, it.y + 64);
-            const uint32_t e0 = off[c], e1 = e0 + cnt[c];
+            const uint32_t e0 = off[c] + uint32_t(wave), e1 = off[c] + cnt[c];
             for (int base = it.y; base < end;) {
                 const int E = piece_lanes(end - base), b0 = base;
                 base += E;
@@ -650,20 +658,22 @@ k_p2p64_list(P2PArgs a, int nitem, const int2 *__restrict__ items, const int32_t
                 // the next entry's record is fetched while the current one's sources are evaluated
                 P2PMeta mn{};
                 if (e1 > e0) mn = meta[e0];
-                for (uint32_t e = e0; e < e1; ++e) {
+                for (uint32_t e = e0; e < e1; e += kP2PWaves) {
                     const P2PMeta m = mn;
-                    mn = meta[e + 1 < e1 ? e + 1 : e];
+                    mn = meta[e + kP2PWaves < e1 ? e + kP2PWaves : e];
                     const double tx = me.dx - m.dx, ty = me.dy - m.dy, tz = me.dz - m.dz;
                     if (E == 64) pol.uniform(parts, m.js, m.je, tx, ty, tz, A);
                     else pol.grouped(parts, m.js + grp, m.je, ng, tx, ty, tz, A);
                 }
-                double f[kNearRows];
-                for_rows([&](auto kc) {
-                    constexpr int K = decltype(kc)::value;
-                    f[K] = pol.template value<K>(A);
-                    for (int o = E; o < 64; o <<= 1) f[K] += __shfl_xor(f[K], o);
-                }, std::make_integer_sequence<int, kNearRows>{});
-                finish(a, gi, write, [&](int r) { return f[r]; });
+                auto sum = [&](auto kc) {
+                    double v = pol.template value<decltype(kc)::value>(A);
+                    for (int o = E; o < 64; o <<= 1) v += __shfl_xor(v, o);
+                    return v;
+                };
+                for_rows([&](auto rc) {
+                    wave_round<decltype(rc)::value>(red, sum, [&](int r, double v) { fin[r * 64 + lane] = v; });
+                }, std::make_integer_sequence<int, kNearRows / kRedRows>{});
+                if (wave == 0) finish(a, gi, write, [&](int r) { return fin[64 * r + lane]; });
             }
         }
     }
@@ -708,10 +718,11 @@ hipError_t launch_p2p64_list(hipStream_t s, const P2PArgs &a, int nitem, const i
     if (nitem == 0) return hipSuccess;
     // a.w: the root's width, the largest a leaf can have
     const bool tab = a.sigma >= 0x1p-100 * a.w;
-    const int wgs = std::min(p2p_slots(false), (nitem + kP2PWaves - 1) / kP2PWaves);
-    hipLaunchKernelGGL(tab ? k_p2p64_list<true> : k_p2p64_list<false>, dim3(unsigned(wgs)), dim3(kP2PThreads),
-                       tab ? PairTab<double>::bytes : 0, s, a, nitem, items, lcell, lstart, off, cnt, meta, parts,
-                       ctr);
+    const int wgs = std::min(p2p_slots(false), nitem);
+    const auto k = tab ? k_p2p64_list<true> : k_p2p64_list<false>;
+    const size_t smem = (tab ? PairTab<double>::bytes : 0) + sizeof(double) * kRedDoubles;
+    hipLaunchKernelGGL(k, dim3(unsigned(wgs)), dim3(kP2PThreads), smem, s, a, nitem, items, lcell, lstart, off, cnt,
+                       meta, parts, ctr);
     return hipGetLastError();
 }
 

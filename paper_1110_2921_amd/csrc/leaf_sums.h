@@ -97,6 +97,27 @@ __device__ __forceinline__ void for_rows(F &&f, std::integer_sequence<int, K...>
     (f(IC<K>{}), ...);
 }
 
+// Rows kRedRows R .. of the waves' sums sum(row), added through LDS in wave order;
+// put(row, x) gets the lane's total in the threads below 64 kRedRows
+template <int R, class F, class G>
+__device__ __forceinline__ void wave_round(double *red, F sum, G put) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    for_rows([&](auto kc) {
+        constexpr int k = decltype(kc)::value;
+        red[(k * kP2PWaves + wave) * 64 + lane] = sum(IC<R * kRedRows + k>{});
+    }, std::make_integer_sequence<int, kRedRows>{});
+    __syncthreads();
+    if (tid < 64 * kRedRows) {
+        const int k = tid >> 6;
+        double x = 0.0;
+#pragma unroll
+        for (int q = 0; q < kP2PWaves; ++q) x += red[(k * kP2PWaves + q) * 64 + lane];
+        put(R * kRedRows + k, x);
+    }
+    __syncthreads();
+}
+
 // u, J and dalpha/dt of sorted target gi from its near sums f(row), with the
 // far field where there is one, in caller order
 template <class F>
@@ -219,21 +240,10 @@ __device__ __forceinline__ void p2p_leaves(const P2PArgs &a, const typename POL:
             } else {
                 // then the waves', kRedRows values a round
                 auto round = [&](auto rc) {
-                    constexpr int r0 = decltype(rc)::value * kRedRows;
-                    for_rows([&](auto kc) {
-                        constexpr int k = decltype(kc)::value;
-                        red[(k * kP2PWaves + wave) * 64 + lane] = sum(IC<r0 + k>{});
-                    }, std::make_integer_sequence<int, kRedRows>{});
-                    __syncthreads();
-                    if (tid < 64 * kRedRows) {
-                        const int k = tid >> 6;
-                        double x = 0.0;
-#pragma unroll
-                        for (int q = 0; q < kP2PWaves; ++q) x += red[(k * kP2PWaves + q) * 64 + lane];
-                        if (!a.near) fin[(r0 + k) * 64 + lane] = x;
-                        else if (write) a.near[(size_t(blockIdx.z) * kNearRows + r0 + k) * n + gi] = x;
-                    }
-                    __syncthreads();
+                    wave_round<decltype(rc)::value>(red, sum, [&](int r, double x) {
+                        if (!a.near) fin[r * 64 + lane] = x;
+                        else if (write) a.near[(size_t(blockIdx.z) * kNearRows + r) * n + gi] = x;
+                    });
                 };
                 round(IC<0>{});
                 if (all)
