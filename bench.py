@@ -37,7 +37,7 @@ PEAKS = {  # MI355X published peaks
     "valu_f64_tflops": 78.6,
 }
 # Algorithmic work per unit, FMA = 2 flop:
-P2P_FLOP_PER_PAIR = {"mixed": 79.0, "fp64": 69.0}   # counted from the pair kernels
+P2P_FLOP_PER_PAIR = {"mixed": 67.0, "fp64": 78.0}   # counted from the pair kernels (table form)
 # Gaussian sum: r = t - s (3), |r|^2 (5), scale (1), exp2 (1), three strength FMAs (6)
 GAUSS_FLOP_PER_PAIR = 16.0
 # The paper's base run (Sec. 4.1): time step (forward Euler in its loop),
@@ -395,22 +395,22 @@ def main():
     p2p_flop = P2P_FLOP_PER_PAIR[args.precision] * pairs
     f32 = args.precision == "mixed"
     esz = 4 if f32 else 8
-    # FP32 at p = 10: the orbit kernel from level 4 on (class-major pack of the
-    # multipoles first), dense operator-stationary MFMAs below
-    orbit = w.p == 10 and w.level >= 4
+    # p = 6, 8, 10: the orbit form at every level (class-major pack of the multipoles
+    # first), levels 1 to 3 in one launch
+    orbit = w.p in (6, 8, 10)
     lev0 = 1 if w.periodic else 2
     if orbit:
-        m2l_kernel = ("k_m2l_sym<10> (levels 4+) + k_m2l_os<4,8,false> (levels < 4) + k_sym_pack" if f32 else
-                      "k_m2l_sym64<10> (levels 4+) + k_translate<double,1,1,0,24> (levels < 4) + k_sym_pack")
-        per_t = orbit_m2l_flop_per_target(w.p)
-        m2l_flop = sum(8 ** l * (per_t if l >= 4 else 6.0 * C * C * 189) for l in range(lev0, w.level + 1))
+        m2l_kernel = (f"k_m2l_sym<{w.p}> (levels 4+) + k_m2l_orbits (levels < 4) + k_sym_pack" if f32 else
+                      f"k_m2l_sym64<{w.p}> (levels 4+) + k_m2l_orbits (levels < 4) + k_sym_pack")
+        m2l_flop = sum(8 ** l for l in range(lev0, w.level + 1)) * orbit_m2l_flop_per_target(w.p)
     else:
         m2l_kernel = "k_translate<double,1,1,0,24>" if not f32 else "k_m2l_os"
     # HBM bytes of the whole M2L phase per evaluation (every launch of its kernels)
     m2l_traffic = measured_phase_bytes(w.name, args.precision,
-                                       ("k_m2l_sym<", "k_m2l_os", "k_sym_pack<float>", "k_split_reduce<float>")
-                                       if f32 else ("k_m2l_sym64", "k_translate<double,1,1,0,", "k_sym_pack<double>",
-                                                    "k_split_reduce<double>"))
+                                       ("k_m2l_sym<", "k_m2l_orbits<float", "k_m2l_os", "k_sym_pack<float>",
+                                        "k_split_reduce<float>")
+                                       if f32 else ("k_m2l_sym64", "k_m2l_orbits<double", "k_translate<double,1,1,0,",
+                                                    "k_sym_pack<double>", "k_split_reduce<double>"))
     # algorithmic bytes of the M2L phase: read M, read and write L at every level, the operators once
     cells = sum(8 ** l for l in range(lev0, w.level + 1))
     m2l_alg_bytes = cells * 3 * C * esz * 3 + 316 * C * C * esz
@@ -420,7 +420,7 @@ def main():
                 "peak": PEAKS["mfma_f32_tflops" if f32 else "mfma_f64_tflops"], "unit": "TFLOP/s",
                 "traffic": m2l_traffic, "traffic_unit": "bytes per evaluation",
                 "algorithmic_bytes_per_eval": m2l_alg_bytes, "launches_per_eval": m2l_launch}
-    sym_name = "k_m2l_sym<10>" if f32 else "k_m2l_sym64<10>"
+    sym_name = f"k_m2l_sym<{w.p}>" if f32 else f"k_m2l_sym64<{w.p}>"
     fin = measured_finest_launch(w.name, args.precision, sym_name) if orbit else None
     if fin:
         roof_m2l["finest_level_launch"] = {"kernel": sym_name, "grid_size": fin[0], "hbm_bytes": fin[1],
