@@ -37,7 +37,7 @@ CALIBRATION_BYTES = 1 << 30
 # the sources the profiled kernels (tree, expansions, translations, near field)
 # and their launch configurations are built from
 MEASURED_SOURCES = ("kernels.h", "device_harmonics.h", "kernels_tree.hip", "kernels_fmm.hip", "kernels_p2p.hip",
-                    "kernels_m2l_sym.hip", "operators.h", "operators.cpp", "vmfmm.cpp")
+                    "kernels_m2l_sym.hip", "leaf_sums.h", "operators.h", "operators.cpp", "vmfmm.cpp")
 
 
 def sources_sha256() -> str:
