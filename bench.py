@@ -625,7 +625,7 @@ def main():
         ctx.set_timing(False)
         gauss_ms = ph["gauss"][0] / ph["gauss"][1]
         products = ph["gauss"][1] / reps
-        gauss_kernel = "k_gauss<float,vmfmm::Part32>" if f32 else "k_gauss<double,vmfmm::Part64>"
+        gauss_kernel = "k_gauss<float,vmfmm::Part32,false>" if f32 else "k_gauss<double,vmfmm::Part64,false>"
         roof_gauss = {"bound": "alu", "kernel": gauss_kernel + " (with the strength packing)",
                       "achieved": GAUSS_FLOP_PER_PAIR * pairs / (gauss_ms * 1e-3) / 1e12,
                       "peak": PEAKS["valu_f32_tflops" if f32 else "valu_f64_tflops"], "unit": "TFLOP/s",

@@ -33,7 +33,6 @@ namespace vmfmm {
 
 namespace {
 
-using dev::irregular_packed;
 using dev::irregular_packed_orders;
 
 __device__ __forceinline__ int ad_coord(uint32_t k, int d, int level) {
@@ -452,27 +451,34 @@ __global__ void __launch_bounds__(64) k_ad_traverse(AdTreeView t, AdLists ls, in
 }
 
 // ------------------------------------------------------------ cell-particle ----
-// P2L: one workgroup per target cell with a P2L list.  Lane j takes the
-// conjugated irregular harmonics of source particle j (relative to the target
-// centre, in target widths) into its LDS row; lanes then sum the rows per
-// coefficient, weighted by the particles' strengths, and add the result to the
-// cell's local expansion (which already holds its M2L).
-__global__ void __launch_bounds__(64) k_ad_p2l(AdTreeView t, AdLists ls, int off, int ncl, int ncell, int p, int kp,
-                                               DevTables tab, const Part64 *__restrict__ parts,
-                                               double *__restrict__ L) {
+// P2L: one workgroup of 4 waves per target cell with a P2L list.  Four lanes per
+// source particle take the conjugated irregular harmonics (relative to the target
+// centre, in target widths; lane j the orders m = j (mod 4)) into the particle's LDS
+// row; then thread (q, g) sums coefficients q, q + 64, ... over the particles g, g + 4,
+// ... of each batch, weighted by their strengths, and the four partial sums of a
+// coefficient are added to the cell's local expansion (which already holds its
+// M2L).  The rows' LDS leaves two workgroups a compute unit, so what counts is how
+// many lanes share the recurrences: with one wave and a particle a lane 292 us (2^19
+// clustered particles, p = 10), now 182; 20011 periodic, p = 6: 92 and 72; rows of 32
+// or 16 particles, more workgroups a unit, were slower than rows of 64.
+constexpr int kP2LThreads = 256;
+__global__ void __launch_bounds__(kP2LThreads) k_ad_p2l(AdTreeView t, AdLists ls, int off, int ncl, int ncell, int p,
+                                                        int kp, DevTables tab, const Part64 *__restrict__ parts,
+                                                        double *__restrict__ L) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     const int a = off + blockIdx.x;
     const uint32_t e0 = ls.off[size_t(2) * ncell + a];
     const uint32_t e1 = e0 + ls.cnt[size_t(2) * ncell + a];
     if (e1 == e0) return;
-    const int C = (p + 1) * (p + 1), lane = threadIdx.x;
+    const int C = (p + 1) * (p + 1), tid = threadIdx.x;
+    const int pi = tid >> 2, j4 = tid & 3, q0 = tid & 63, g = tid >> 6;
     const int stride = C + 1;
     double *rows = reinterpret_cast<double *>(smem_raw);   // [64][C + 1]
     double *al = rows + 64 * stride;                       // [64][3]
     double ca[3];
     centre(t, a, ca);
     const double inv_w = ldexp(t.inv_len, t.level[a]);
-    constexpr int kMaxC = 4;   // coefficients per lane: C <= 256 (p <= 15)
+    constexpr int kMaxC = 4;   // coefficients per thread: C <= 256 (p <= 15)
     double acc[kMaxC][3];
     for (int q = 0; q < kMaxC; ++q) acc[q][0] = acc[q][1] = acc[q][2] = 0.0;
     for (uint32_t e = e0; e < e1; ++e) {
@@ -485,19 +491,23 @@ __global__ void __launch_bounds__(64) k_ad_p2l(AdTreeView t, AdLists ls, int off
         const int s0 = t.start[b], cnt = t.count[b];
         for (int base = 0; base < cnt; base += 64) {
             const int nj = min(64, cnt - base);
-            if (lane < nj) {
-                const Part64 q = parts[s0 + base + lane];
+            if (pi < nj) {
+                const Part64 q = parts[s0 + base + pi];
                 const double X = (q.dx + sh[0]) * inv_w, Y = (q.dy + sh[1]) * inv_w, Z = (q.dz + sh[2]) * inv_w;
-                irregular_packed<double>(X, Y, Z, p, tab.c1_64, tab.c2_64, tab.diag_64, -1.0, rows + lane * stride, 1);
-                al[lane * 3 + 0] = q.ax;
-                al[lane * 3 + 1] = q.ay;
-                al[lane * 3 + 2] = q.az;
+                irregular_packed_orders<double>(X, Y, Z, p, tab.c1_64, tab.c2_64, tab.diag_64, -1.0, j4, 4,
+                                                rows + pi * stride, 1);
+                if (j4 == 0) {
+                    al[pi * 3 + 0] = q.ax;
+                    al[pi * 3 + 1] = q.ay;
+                    al[pi * 3 + 2] = q.az;
+                }
             }
             __syncthreads();
+#pragma unroll
             for (int q = 0; q < kMaxC; ++q) {
-                const int cidx = lane + 64 * q;
+                const int cidx = q0 + 64 * q;
                 if (cidx >= C) break;
-                for (int j = 0; j < nj; ++j) {
+                for (int j = g; j < nj; j += 4) {
                     const double v = rows[j * stride + cidx];
                     acc[q][0] += al[j * 3 + 0] * v;
                     acc[q][1] += al[j * 3 + 1] * v;
@@ -507,10 +517,20 @@ __global__ void __launch_bounds__(64) k_ad_p2l(AdTreeView t, AdLists ls, int off
             __syncthreads();
         }
     }
+    // the waves' partial sums, in wave order, through the rows' LDS: 4 x 3 x 64
+    // values at a time, below 64 rows for any degree
+#pragma unroll
     for (int q = 0; q < kMaxC; ++q) {
-        const int cidx = lane + 64 * q;
-        if (cidx >= C) break;
-        for (int k = 0; k < 3; ++k) L[(size_t(a) * 3 + k) * kp + cidx] += acc[q][k];
+        if (64 * q >= C) break;
+        for (int k = 0; k < 3; ++k) rows[(g * 3 + k) * 64 + q0] = acc[q][k];
+        __syncthreads();
+        const int cidx = q0 + 64 * q;
+        if (g < 3 && cidx < C) {
+            double x = 0.0;
+            for (int w = 0; w < 4; ++w) x += rows[(w * 3 + g) * 64 + q0];
+            L[(size_t(a) * 3 + g) * kp + cidx] += x;
+        }
+        __syncthreads();
     }
 }
 
@@ -808,8 +828,9 @@ hipError_t launch_ad_traverse(hipStream_t s, const AdTreeView &t, const AdLists 
 hipError_t launch_ad_p2l(hipStream_t s, const AdTreeView &t, const AdLists &ls, int off, int ncl, int ncell, int p,
                          int kp, const DevTables &tab, const Part64 *parts, double *L) {
     const int C = (p + 1) * (p + 1);
-    const size_t smem = sizeof(double) * (size_t(64) * (C + 1) + 64 * 3);
-    hipLaunchKernelGGL(k_ad_p2l, dim3(ncl), dim3(64), smem, s, t, ls, off, ncl, ncell, p, kp, tab, parts, L);
+    // the reduction takes 12 x 64 doubles of it
+    const size_t smem = sizeof(double) * std::max<size_t>(size_t(64) * (C + 1) + 64 * 3, 12 * 64);
+    hipLaunchKernelGGL(k_ad_p2l, dim3(ncl), dim3(kP2LThreads), smem, s, t, ls, off, ncl, ncell, p, kp, tab, parts, L);
     return hipGetLastError();
 }
 
