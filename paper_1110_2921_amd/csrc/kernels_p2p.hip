@@ -252,6 +252,7 @@ typedef const __attribute__((address_space(3))) char *LdsBytes;
 
 template <typename T> struct PairTab;
 template <> struct PairTab<double> {
+    typedef dbl2 Vec;   // 16 bytes
     static constexpr int seg = kPairSeg64, rows = pair_rows(kPairSeg64);
     static constexpr int bytes = rows * 8 * kPairCoefs64;
     static constexpr int mant = 20, bias = 1023;   // of the high word
@@ -280,6 +281,7 @@ template <> struct PairTab<double> {
     static __device__ __forceinline__ double scale(double v, int e) { return ldexp(v, e); }
 };
 template <> struct PairTab<float> {
+    typedef flt4 Vec;
     static constexpr int seg = kPairSeg32, rows = pair_rows(kPairSeg32);
     static constexpr int bytes = rows * 16 * 2;
     static constexpr int mant = 23, bias = 127;
@@ -472,6 +474,14 @@ struct Pol64 {
 // 1e-7 of the block's terms.
 constexpr int kKahanBlock = 16;
 
+// FP32 table: Q and Q' times 2^fold.  A term in units of sigma, Q' (alpha x r) r, has
+// the magnitude sigma^5 alpha / r^3, which leaves FP32's range for cores far below
+// the leaf or small units long before alpha / r^3 does; about sigma^-4 more and the
+// velocity's and the gradient's terms are within a factor sigma of those in physical
+// units.  A power of two: no result in range changes.  The limits keep the
+// coefficients normal (largest 0.27, smallest that counts 2^-60).
+__device__ __forceinline__ int fold32(double sigma) { return min(100, max(-64, -4 * ilogb(sigma))); }
+
 template <bool TAB>
 struct Pol32 {
     using Rec = Part32;
@@ -494,7 +504,7 @@ struct Pol32 {
         if constexpr (TAB) {
             const double is = 1.0 / sigma;
             inv_s2 = float(is * is);
-            cu = is * is * is;
+            cu = ldexp(is * is * is, -fold32(sigma));
             cj = 2.0 * cu * is * is;
         } else {
             k = consts32(sigma);
@@ -575,14 +585,17 @@ struct Pol32 {
     }
 };
 
-// Copies the table to the start of the dynamic LDS; what the policies take for it.
+// Copies the table (FP32: folded) to the start of the dynamic LDS; what the policies
+// take for it.
 template <typename T, bool TAB>
-__device__ __forceinline__ uint32_t load_table(const void *table) {
+__device__ __forceinline__ uint32_t load_table(const P2PArgs &a) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     if constexpr (TAB) {
-        const dbl2 *src = reinterpret_cast<const dbl2 *>(table);
-        dbl2 *dst = reinterpret_cast<dbl2 *>(smem_raw);
-        for (int i = threadIdx.x; i < PairTab<T>::bytes / 16; i += kP2PThreads) dst[i] = src[i];
+        typedef typename PairTab<T>::Vec V;
+        const V *src = reinterpret_cast<const V *>(a.table);
+        V *dst = reinterpret_cast<V *>(smem_raw);
+        const T f = sizeof(T) == 4 ? ldexp(T(1), fold32(a.sigma)) : T(1);
+        for (int i = threadIdx.x; i < PairTab<T>::bytes / 16; i += kP2PThreads) dst[i] = src[i] * f;
         __syncthreads();
     }
     return table_base<T>(uint32_t(uintptr_t((LdsBytes)smem_raw)));
@@ -592,7 +605,7 @@ template <class POL, bool SPLIT, bool TAB>
 __device__ __forceinline__ void p2p_body(const P2PArgs &a, const typename POL::Rec *__restrict__ parts) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     using T = typename POL::Real;
-    p2p_leaves<POL, SPLIT>(a, parts, POL(a.sigma, load_table<T, TAB>(a.table)),
+    p2p_leaves<POL, SPLIT>(a, parts, POL(a.sigma, load_table<T, TAB>(a)),
                            reinterpret_cast<double *>(smem_raw + (TAB ? PairTab<T>::bytes : 0)));
 }
 
@@ -628,7 +641,7 @@ k_p2p64_list(P2PArgs a, int nitem, const int2 *__restrict__ items, const int32_t
              const P2PMeta *__restrict__ meta, const Part64 *__restrict__ parts, int *__restrict__ ctr) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     __shared__ int taken;
-    const Pol64<TAB> pol(a.sigma, load_table<double, TAB>(a.table));
+    const Pol64<TAB> pol(a.sigma, load_table<double, TAB>(a));
     double *red = reinterpret_cast<double *>(smem_raw + (TAB ? PairTab<double>::bytes : 0));
     double *fin = red + kRedRows * kP2PThreads;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -692,8 +705,8 @@ int p2p_shares(int nleaf, int ntarget, bool mixed) {
     return std::max(1, std::min(8, slots / (nleaf * p2p_blocks(nleaf, ntarget, slots))));
 }
 
-// The table needs sigma-unit distances, their powers t^-3/2 and t^-5/2 and, in
-// FP32, 1/sigma^2 within the type's range.
+// The table needs sigma-unit distances, their powers t^-3/2 and t^-5/2 (the terms
+// that these enter: fold32) and, in FP32, 1/sigma^2 within the type's range.
 hipError_t launch_p2p64(hipStream_t s, const P2PArgs &a, const Part64 *parts) {
     const bool tab = a.sigma >= 0x1p-100 * a.w;
     const P2PShape p = p2p_shape(a, p2p_slots(false), tab ? PairTab<double>::bytes : 0);
