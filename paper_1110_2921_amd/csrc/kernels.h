@@ -474,8 +474,14 @@ hipError_t launch_split_reduce64(hipStream_t s, int level, int kp, int C, int ns
 // the same over nelem = cells * 3 * kp elements of dst (the cells of a split launch)
 hipError_t launch_split_reduce64_n(hipStream_t s, int64_t nelem, int kp, int C, int nsplit, const double *part,
                                    double *dst, int accumulate);
-// True if the symmetric M2L kernel is built for degree p.
+// True if the symmetric M2L kernels are built for degree p.
 bool m2l_sym_supported(int p);
+// True if the kernels' 32-bit byte offsets reach the class-major multipoles of `ncell`
+// cells and their zero cell (`elem`: 4 or 8 bytes a coefficient): uniform levels up to 7 in
+// FP32 and 6 in FP64, 1398100 adaptive cells at p = 6 and 8, 1242755 at p = 10.
+inline bool m2l_sym_fits(int p, int64_t ncell, size_t elem) {
+    return (uint64_t(ncell) + 1) * 3 * 16 * sym_layout(p).nblk * elem <= uint64_t(1) << 32;
+}
 // M2L at `level` (FP32): dst[cell] (+)= sum over the interaction list, from the
 // class-major multipoles mc of the level (zero_cell: index of a zero cell,
 // relative to mc), operators ops (per octant, orbit-compact, offsets op_off

@@ -809,7 +809,7 @@ hipError_t m2l_sym64(hipStream_t s, int level, int periodic, int kp, const doubl
     if (level < 1) return hipErrorInvalidValue;
     constexpr SymLayout SL = sym_layout(P);
     constexpr int KC = 16 * SL.nblk;
-    if ((uint64_t(zero_cell) + 1) * 3 * KC * sizeof(double) > (uint64_t(1) << 32)) return hipErrorInvalidValue;
+    if (!m2l_sym_fits(P, zero_cell, sizeof(double))) return hipErrorInvalidValue;
     const int64_t ncell_t = int64_t(1) << (3 * (level - 1));
     const size_t smem = sizeof(double) * size_t(kRing) * size_t(16 * SL.C + 32);
     const int tiles = int((ncell_t + kSymTargets - 1) / kSymTargets) * 8;
@@ -839,7 +839,7 @@ hipError_t m2l_sym64_adaptive(hipStream_t s, int kp, const double *mc, int64_t z
                               int accumulate, const SymAdapt &ad_in, double *part, size_t part_elems) {
     constexpr SymLayout SL = sym_layout(P);
     constexpr int KC = 16 * SL.nblk;
-    if ((uint64_t(zero_cell) + 1) * 3 * KC * sizeof(double) > (uint64_t(1) << 32)) return hipErrorInvalidValue;
+    if (!m2l_sym_fits(P, zero_cell, sizeof(double))) return hipErrorInvalidValue;
     SymAdapt ad = ad_in;
     ad.tile_start[0] = 0;
     for (int o = 0; o < 8; ++o) ad.tile_start[o + 1] = ad.tile_start[o] + (ad.oct_n[o] + kSymTargets - 1) / kSymTargets;
@@ -889,7 +889,7 @@ hipError_t launch_m2l_orbits(hipStream_t s, int lo, int hi, int periodic, int p,
         constexpr int P = decltype(pc)::value;
         constexpr SymLayout SL = sym_layout(P);
         constexpr int RS = 2;
-        if ((uint64_t(zero_cell) + 1) * 48 * SL.nblk * sizeof(T) > (uint64_t(1) << 32)) return hipErrorInvalidValue;
+        if (!m2l_sym_fits(P, zero_cell, sizeof(T))) return hipErrorInvalidValue;
         hipLaunchKernelGGL((k_m2l_orbits<T, P, RS>), dim3(unsigned(n), RS), dim3(kOrbThreads), 0, s, lv, periodic, kp,
                            mc, uint32_t(zero_cell * 48 * SL.nblk), ops, op_off, f32 ? 1 : SL.nblk,
                            f32 ? kSymOrbits + 1 : kSymOrbits * SL.nblk + 1, orbits, row_std, dst);
@@ -911,8 +911,7 @@ hipError_t m2l_sym32(hipStream_t s, int level, int periodic, int kp, const float
     if (level < 1) return hipErrorInvalidValue;
     constexpr SymLayout SL = sym_layout(P);
     constexpr int KC = 16 * SL.nblk;
-    // byte offsets into mc (the zero cell included) must fit 32 bits
-    if ((uint64_t(zero_cell) + 1) * 3 * KC * sizeof(float) > (uint64_t(1) << 32)) return hipErrorInvalidValue;
+    if (!m2l_sym_fits(P, zero_cell, sizeof(float))) return hipErrorInvalidValue;
     const int64_t ncell_t = int64_t(1) << (3 * (level - 1));
     const size_t smem = 2 * sizeof(float) * size_t(16 * SL.C * SL.nblk + 64);
     const int tiles = int((ncell_t + kSymTargets - 1) / kSymTargets) * 8;

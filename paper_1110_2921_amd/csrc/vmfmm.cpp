@@ -890,6 +890,15 @@ vm_status sym_m2l(vm_ctx *ctx, int lo, int hi, int periodic, int p, int kp, cons
     return VM_OK;
 }
 
+// Square-truncation M2L of a uniform tree by reflection orbits where its kernels are
+// built and reach the tree's cells
+bool uniform_sym(const vm_opts *opts, int p, int level) {
+    const int periodic = opts->periodic > 0, mixed = opts->precision == VM_MIXED;
+    const int64_t ncells = ((int64_t(1) << (3 * (level + 1))) - 1) / 7;
+    return opts->truncation != VM_TRIANGULAR && m2l_sym_supported(p) && level >= (periodic ? 1 : 2) &&
+           m2l_sym_fits(p, ncells, mixed ? sizeof(float) : sizeof(double));
+}
+
 // One evaluation (the launch sequence of Sec. 3.1): tree, upward pass,
 // lattice, downward pass, then L2P and P2P at the particles (y == nullptr)
 // or at the m points y, which get a tree of their own (then no stretching).
@@ -908,11 +917,8 @@ vm_status fmm_impl(vm_ctx *ctx, int64_t n, const double *x, const double *alpha,
     if (vm_status st = ensure_ops(ctx, p, &ops); st != VM_OK) return st;
     if (opts->truncation == VM_TRIANGULAR)
         if (vm_status st = ensure_tri_ops(ctx, ops, 0); st != VM_OK) return st;
-    // square-truncation M2L by reflection orbits where its kernels are built (their
-    // source offsets are 32-bit byte offsets: levels up to 7 in FP32, 6 in FP64)
     const int lmin = periodic ? 0 : 2, lm2l = periodic ? 1 : 2;   // coarsest levels with multipoles, with M2L
-    const bool use_sym = opts->truncation != VM_TRIANGULAR && m2l_sym_supported(p) && level >= lm2l &&
-                         level <= (mixed ? 7 : 6);
+    const bool use_sym = uniform_sym(opts, p, level);
     if (use_sym)
         if (vm_status st = ensure_sym_ops(ctx, ops, 0); st != VM_OK) return st;
     const double *tlat = nullptr;
@@ -1234,10 +1240,6 @@ vm_status adaptive_impl(vm_ctx *ctx, int64_t n64, const double *x, const double 
     if (K >= 2)
         if (vm_status st = ensure_lattice(ctx, p, K, &tlat); st != VM_OK) return st;
     if (vm_status st = ensure_ad_tables(ctx, p); st != VM_OK) return st;
-    // M2L by reflection orbits at the levels with enough cells (p = 10)
-    const bool ad_sym = m2l_sym_supported(p);
-    if (ad_sym)
-        if (vm_status st = ensure_sym_ops(ctx, ops, 0); st != VM_OK) return st;
     const int C = ncoef(p), kp = coef_stride(C);
     A.valid = false;
     ++ctx->tree_gen;
@@ -1294,6 +1296,10 @@ vm_status adaptive_impl(vm_ctx *ctx, int64_t n64, const double *x, const double 
     if (ncl > 0) VM_HIP(launch_ad_no_children(s, t, off, ncl), "adaptive last level");
     const int ncell = lo.back();
     const int nlev = int(lo.size()) - 1;
+    // M2L by reflection orbits, all levels; beyond its kernels' reach the dense operators
+    const bool ad_sym = m2l_sym_supported(p) && m2l_sym_fits(p, ncell, sizeof(double));
+    if (ad_sym)
+        if (vm_status st = ensure_sym_ops(ctx, ops, 0); st != VM_OK) return st;
 
     // --- leaves in particle order and the sorted records -----------------------
     VM_HIP(A.leaf_at.reserve(sizeof(int32_t) * size_t(n)), "alloc leaves");
@@ -1702,8 +1708,7 @@ vm_status adjoint_impl(vm_ctx *ctx, int64_t n, const double *x, const double *al
         if (vm_status e = ensure_lattice_t(ctx, p, K, &tlat_t); e != VM_OK) return e;
     // the adjoint M2L by reflection orbits where the forward one runs so
     const int lm2l = periodic ? 1 : 2;
-    const bool use_sym = opts->truncation != VM_TRIANGULAR && m2l_sym_supported(p) && level >= lm2l &&
-                         level <= (mixed ? 7 : 6);
+    const bool use_sym = uniform_sym(opts, p, level);
     const int64_t ncells = ((int64_t(1) << (3 * (level + 1))) - 1) / 7;
     if (use_sym) {
         if (vm_status e = ensure_sym_ops(ctx, ops, 1); e != VM_OK) return e;
