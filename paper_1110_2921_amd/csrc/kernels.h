@@ -178,7 +178,8 @@ constexpr int pair_rows(int seg) { return ((kPairTabHi - kPairTabLo) << seg) + 1
 // workgroup per leaf
 constexpr int kP2PSplitLeaves = 1 << 15;
 // shares a launch with a near buffer splits its sources into (see P2PArgs::near)
-int p2p_shares(int nleaf, int ntarget, bool mixed);
+constexpr int kP2PMaxShares = 8;
+int p2p_shares(int nleaf, int ntarget, int nsource, bool mixed);
 hipError_t launch_p2p64(hipStream_t s, const P2PArgs &a, const Part64 *parts);
 hipError_t launch_p2p32(hipStream_t s, const P2PArgs &a, const Part32 *parts);
 

@@ -700,9 +700,14 @@ using P2PKernel = void (*)(P2PArgs, const R *);
 // workgroups the chip holds at once (80 / 128 registers per lane)
 static int p2p_slots(bool mixed) { return compute_units() * (mixed ? 3 : 2); }
 
-int p2p_shares(int nleaf, int ntarget, bool mixed) {
+// Shares that fill the chip, but no fewer than 16 sources a wave: a share costs a
+// copy of the table and a term of every L2P sum (768 particles at level 2 in FP64:
+// 26 us with 2 shares, 34 with 8).
+int p2p_shares(int nleaf, int ntarget, int nsource, bool mixed) {
     const int slots = p2p_slots(mixed);
-    return std::max(1, std::min(8, slots / (nleaf * p2p_blocks(nleaf, ntarget, slots))));
+    const int64_t per_wave = int64_t(27) * nsource / nleaf / kP2PWaves;
+    const int most = int(std::min<int64_t>(kP2PMaxShares, per_wave / 16));
+    return std::max(1, std::min(most, slots / (nleaf * p2p_blocks(nleaf, ntarget, slots))));
 }
 
 // The table needs sigma-unit distances, their powers t^-3/2 and t^-5/2 (the terms

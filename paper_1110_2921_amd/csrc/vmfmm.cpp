@@ -930,7 +930,7 @@ vm_status fmm_impl(vm_ctx *ctx, int64_t n, const double *x, const double *alpha,
     const size_t esz = mixed ? sizeof(float) : sizeof(double);
     const int64_t ncells = ((int64_t(1) << (3 * (level + 1))) - 1) / 7;
     VM_HIP(ctx->far.reserve(sizeof(double) * 12 * size_t(mi)), "alloc far field");
-    const int shares = p2p_shares(int(nleaf), mi, mixed);
+    const int shares = p2p_shares(int(nleaf), mi, ni, mixed);
     VM_HIP(ctx->nearf.reserve(sizeof(double) * 15 * size_t(mi) * shares), "alloc near field");
     VM_HIP(ctx->trpart.reserve(kTrPartBytes), "alloc split partials");
     if (ctx->zeros.bytes == 0) VM_HIP(ctx->zeros.reserve(tr_zero_elems(coef_stride(ncoef(VM_MAX_P))) * sizeof(double), true),
