@@ -489,8 +489,10 @@ void pair_exact(long double t, long double &q, long double &dq) {
         }
         return;
     }
-    const long double rho = sqrtl(t), e = expl(-0.5L * t);
-    q = (erfl(rho * sqrtl(0.5L)) - c * rho * e) / (rho * t);
+    const long double rho = sqrtl(t);
+    // from t = 128 on erfc and the exponential are below the last bit of either sum
+    const long double e = t < 128.0L ? expl(-0.5L * t) : 0.0L;
+    q = (t < 128.0L ? erfl(rho * sqrtl(0.5L)) - c * rho * e : 1.0L) / (rho * t);
     dq = (c * e - 3.0L * q) / t;
 }
 
@@ -506,6 +508,11 @@ std::vector<long double> pair_rows_of(int lseg, int nc) {
     T[1][1] = 1.0L;
     for (int n = 2; n <= D; ++n)
         for (int i = 0; i <= D; ++i) T[n][i] = (i > 0 ? 2.0L * T[n - 1][i - 1] : 0.0L) - T[n - 2][i];
+    long double node[NN], basis[DM + 1][NN];
+    for (int k = 0; k < NN; ++k) {
+        node[k] = cosl(pi * (k + 0.5L) / NN);
+        for (int n = 0; n <= D; ++n) basis[n][k] = cosl(pi * n * (k + 0.5L) / NN);
+    }
     const int seg = 1 << lseg;
     for (int r = 0; r < R; ++r) {
         // segment [a, b] and the centre c the kernel forms from the index bits
@@ -523,10 +530,10 @@ std::vector<long double> pair_rows_of(int lseg, int nc) {
         }
         const long double m = 0.5L * (a + b), h = 0.5L * (b - a);
         long double v[NN], cheb[DM + 1], q, dq;
-        for (int k = 0; k < NN; ++k) pair_exact(m + h * cosl(pi * (k + 0.5L) / NN), q, v[k]);
+        for (int k = 0; k < NN; ++k) pair_exact(m + h * node[k], q, v[k]);
         for (int n = 0; n <= D; ++n) {
             cheb[n] = 0.0L;
-            for (int k = 0; k < NN; ++k) cheb[n] += v[k] * cosl(pi * n * (k + 0.5L) / NN);
+            for (int k = 0; k < NN; ++k) cheb[n] += v[k] * basis[n][k];
             cheb[n] *= (n == 0 ? 1.0L : 2.0L) / NN;
         }
         // in y = (t - m) / h, then about x = t - c: y = (x + s) / h, s = c - m

@@ -81,18 +81,22 @@ void swizzle(const std::vector<double> &m, int C, std::vector<T> &out, size_t ba
 
 struct OpSet {
     int p = -1;
-    DevBuf m2l64, m2l32, m2m64, m2m32, l2l64, l2l32;
+    DevBuf m2m64, m2m32, l2l64, l2l32;
     DevBuf c1_64, c2_64, dg_64, c1_32, c2_32, dg_32;
     DevBuf l2p_idx, l2p_w64, l2p_w32;
     int width = 0, nu = 0, ng = 0;
     // adjoint: transposed operators and tables (built on first use)
     bool adj_ready = false;
-    DevBuf m2lT64, m2lT32, m2mT64, m2mT32, l2lT64, l2lT32;
+    DevBuf m2mT64, m2mT32, l2lT64, l2lT32;
     DevBuf t_idx, t_w64, t_w32, g_idx, g_w64, g_w32;
     int width_t = 0, width_g = 0;
-    // M2L operators truncated to n + n' <= p, and their transposes (built on first use)
-    bool tri_ready = false, tri_adj_ready = false;
-    DevBuf m2lt64, m2lt32, m2lTt64, m2lTt32;
+    // dense M2L operators of the 316 offsets, [adjoint][truncated to n + n' <= p]
+    // (built on first use: the reflection-orbit M2L does without)
+    struct DenseM2L {
+        bool ready = false;
+        DevBuf f64, f32;
+    };
+    DenseM2L m2l[2][2];
     // reflection-orbit M2L (square truncation; built on first use): class maps and
     // orbits, and the operators of the forward gather and of the adjoint one
     struct SymOps {
@@ -276,9 +280,16 @@ vm_status ensure_tables(vm_ctx *ctx) {
     const std::vector<int16_t> lists = device_octant_lists();
     VM_HIP(upload(ctx->offsets, offs), "upload offsets");
     VM_HIP(upload(ctx->octlists, lists), "upload octant lists");
-    VM_HIP(upload(ctx->pair_tab64, pair_table64()), "upload pair table");
-    VM_HIP(upload(ctx->pair_tab32, pair_table32()), "upload pair table");
     ctx->tables_ready = true;
+    return VM_OK;
+}
+
+// the near field's pair table of one precision
+vm_status ensure_pair_table(vm_ctx *ctx, int mixed) {
+    DevBuf &b = mixed ? ctx->pair_tab32 : ctx->pair_tab64;
+    if (b.ptr) return VM_OK;
+    if (mixed) VM_HIP(upload(b, pair_table32()), "upload pair table");
+    else VM_HIP(upload(b, pair_table64()), "upload pair table");
     return VM_OK;
 }
 
@@ -292,20 +303,7 @@ vm_status ensure_ops(vm_ctx *ctx, int p, OpSet **out) {
     set->p = p;
     const int C = ncoef(p);
     const size_t frag = tr_frag(C);
-    const OffsetTable &t = offset_table();
     std::vector<double> m(size_t(C) * C);
-    {
-        std::vector<double> o64(316 * frag);
-        std::vector<float> o32(316 * frag);
-        for (int i = 0; i < 316; ++i) {
-            const double D[3] = {-double(t.d[i][0]), -double(t.d[i][1]), -double(t.d[i][2])};
-            m2l_matrix(p, D, 1.0, 1.0, m.data());
-            swizzle(m, C, o64, i * frag);
-            swizzle(m, C, o32, i * frag);
-        }
-        VM_HIP(upload(set->m2l64, o64), "upload M2L");
-        VM_HIP(upload(set->m2l32, o32), "upload M2L");
-    }
     {
         std::vector<double> a64(8 * frag), b64(8 * frag);
         std::vector<float> a32(8 * frag), b32(8 * frag);
@@ -378,26 +376,11 @@ vm_status ensure_adj_ops(vm_ctx *ctx, OpSet *set) {
     const int p = set->p;
     const int C = ncoef(p);
     const size_t frag = tr_frag(C);
-    const OffsetTable &t = offset_table();
     std::vector<double> m(size_t(C) * C), mt(size_t(C) * C);
     auto transpose = [&]() {
         for (int i = 0; i < C; ++i)
             for (int j = 0; j < C; ++j) mt[size_t(j) * C + i] = m[size_t(i) * C + j];
     };
-    {
-        // operator for offset d applied in the adjoint gather is T_{-d}^T
-        std::vector<double> o64(316 * frag);
-        std::vector<float> o32(316 * frag);
-        for (int i = 0; i < 316; ++i) {
-            const double D[3] = {double(t.d[i][0]), double(t.d[i][1]), double(t.d[i][2])};   // target - source of -d
-            m2l_matrix(p, D, 1.0, 1.0, m.data());
-            transpose();
-            swizzle(mt, C, o64, i * frag);
-            swizzle(mt, C, o32, i * frag);
-        }
-        VM_HIP(upload(set->m2lT64, o64), "upload M2L^T");
-        VM_HIP(upload(set->m2lT32, o32), "upload M2L^T");
-    }
     {
         std::vector<double> a64(8 * frag), b64(8 * frag);
         std::vector<float> a32(8 * frag), b32(8 * frag);
@@ -433,14 +416,15 @@ vm_status ensure_adj_ops(vm_ctx *ctx, OpSet *set) {
     return VM_OK;
 }
 
-// M2L operators truncated to n + n' <= p (forward: `adjoint` 0; transposed: 1).
-vm_status ensure_tri_ops(vm_ctx *ctx, OpSet *set, int adjoint) {
-    if (adjoint ? set->tri_adj_ready : set->tri_ready) return VM_OK;
+// Dense M2L operators (adjoint 1: transposed; tri 1: truncated to n + n' <= p).
+vm_status ensure_m2l_ops(vm_ctx *ctx, OpSet *set, int adjoint, int tri) {
+    OpSet::DenseM2L &d = set->m2l[adjoint][tri];
+    if (d.ready) return VM_OK;
     const int p = set->p;
     const int C = ncoef(p);
     const size_t frag = tr_frag(C);
     const OffsetTable &t = offset_table();
-    std::vector<double> m(size_t(C) * C), mt(size_t(C) * C);
+    std::vector<double> m(size_t(C) * C);
     std::vector<double> o64(316 * frag);
     std::vector<float> o32(316 * frag);
     for (int i = 0; i < 316; ++i) {
@@ -448,20 +432,16 @@ vm_status ensure_tri_ops(vm_ctx *ctx, OpSet *set, int adjoint) {
         const double sg = adjoint ? 1.0 : -1.0;
         const double D[3] = {sg * double(t.d[i][0]), sg * double(t.d[i][1]), sg * double(t.d[i][2])};
         m2l_matrix(p, D, 1.0, 1.0, m.data());
-        triangular(m, C, p);
-        if (adjoint) {
+        if (tri) triangular(m, C, p);
+        if (adjoint)
             for (int a = 0; a < C; ++a)
-                for (int b = 0; b < C; ++b) mt[size_t(b) * C + a] = m[size_t(a) * C + b];
-            swizzle(mt, C, o64, i * frag);
-            swizzle(mt, C, o32, i * frag);
-        } else {
-            swizzle(m, C, o64, i * frag);
-            swizzle(m, C, o32, i * frag);
-        }
+                for (int b = a + 1; b < C; ++b) std::swap(m[size_t(a) * C + b], m[size_t(b) * C + a]);
+        swizzle(m, C, o64, i * frag);
+        swizzle(m, C, o32, i * frag);
     }
-    VM_HIP(upload(adjoint ? set->m2lTt64 : set->m2lt64, o64), "upload truncated M2L");
-    VM_HIP(upload(adjoint ? set->m2lTt32 : set->m2lt32, o32), "upload truncated M2L");
-    (adjoint ? set->tri_adj_ready : set->tri_ready) = true;
+    VM_HIP(upload(d.f64, o64), "upload M2L");
+    VM_HIP(upload(d.f32, o32), "upload M2L");
+    d.ready = true;
     return VM_OK;
 }
 
@@ -511,18 +491,23 @@ vm_status ensure_sym_ops(vm_ctx *ctx, OpSet *set, int adjoint) {
     std::vector<float> ops;
     std::vector<double> ops64;
     std::vector<int32_t> off(8 * (kSymOrbits + 1)), sl(8 * (kSymOrbits * NB + 1));
-    std::vector<double> T(size_t(C) * C);
+    // operators of the representative offsets d (source - target): D = target - source;
+    // the adjoint gather takes the transpose of the operator of -d
+    const size_t CC = size_t(C) * C;
+    std::vector<double> Ts(kSymOrbits * CC);
+    for (int j = 0; j < kSymOrbits; ++j) {
+        double *T = &Ts[j * CC];
+        const double sd = adjoint ? 1.0 : -1.0;
+        const double D[3] = {sd * reps[j][0], sd * reps[j][1], sd * reps[j][2]};
+        m2l_matrix(p, D, 1.0, 1.0, T);
+        if (adjoint)
+            for (int r = 0; r < C; ++r)
+                for (int c = r + 1; c < C; ++c) std::swap(T[size_t(r) * C + c], T[size_t(c) * C + r]);
+    }
     for (int o = 0; o < 8; ++o)
         for (int j = 0; j < kSymOrbits; ++j) {
             off[o * (kSymOrbits + 1) + j] = int32_t(ops.size());
-            // operator of the representative offset d (source - target): D = target - source;
-            // the adjoint gather takes the transpose of the operator of -d
-            const double sd = adjoint ? 1.0 : -1.0;
-            const double D[3] = {sd * reps[j][0], sd * reps[j][1], sd * reps[j][2]};
-            m2l_matrix(p, D, 1.0, 1.0, T.data());
-            if (adjoint)
-                for (int r = 0; r < C; ++r)
-                    for (int c = r + 1; c < C; ++c) std::swap(T[size_t(r) * C + c], T[size_t(c) * C + r]);
+            const double *T = &Ts[j * CC];
             const int Z = (orb[j] >> 9) & 7;
             for (int b = 0; b < NB; ++b) {
                 sl[o * (kSymOrbits * NB + 1) + j * NB + b] = int32_t(ops64.size());
@@ -913,14 +898,15 @@ vm_status fmm_impl(vm_ctx *ctx, int64_t n, const double *x, const double *alpha,
     const int64_t nleaf = int64_t(1) << (3 * level);
 
     if (vm_status st = ensure_tables(ctx); st != VM_OK) return st;
+    if (vm_status st = ensure_pair_table(ctx, mixed); st != VM_OK) return st;
     OpSet *ops = nullptr;
     if (vm_status st = ensure_ops(ctx, p, &ops); st != VM_OK) return st;
-    if (opts->truncation == VM_TRIANGULAR)
-        if (vm_status st = ensure_tri_ops(ctx, ops, 0); st != VM_OK) return st;
     const int lmin = periodic ? 0 : 2, lm2l = periodic ? 1 : 2;   // coarsest levels with multipoles, with M2L
     const bool use_sym = uniform_sym(opts, p, level);
-    if (use_sym)
-        if (vm_status st = ensure_sym_ops(ctx, ops, 0); st != VM_OK) return st;
+    const int tri = opts->truncation == VM_TRIANGULAR;
+    if (level >= lm2l)
+        if (vm_status st = use_sym ? ensure_sym_ops(ctx, ops, 0) : ensure_m2l_ops(ctx, ops, 0, tri); st != VM_OK)
+            return st;
     const double *tlat = nullptr;
     if (K >= 2)
         if (vm_status st = ensure_lattice(ctx, p, K, &tlat); st != VM_OK) return st;
@@ -1034,9 +1020,8 @@ vm_status fmm_impl(vm_ctx *ctx, int64_t n, const double *x, const double *alpha,
             const bool f32 = sizeof(T) == 4;
             T *M = ctx->mbuf.as<T>(), *L = ctx->lbuf.as<T>();
             auto lev = [&](T *b, int l) { return b + size_t(((int64_t(1) << (3 * l)) - 1) / 7) * 3 * kp; };
-            const int tri = opts->truncation == VM_TRIANGULAR;
-            const T *m2l = tri ? (f32 ? (const T *)ops->m2lt32.ptr : (const T *)ops->m2lt64.ptr)
-                               : (f32 ? (const T *)ops->m2l32.ptr : (const T *)ops->m2l64.ptr);
+            const OpSet::DenseM2L &dense = ops->m2l[0][tri];
+            const T *m2l = f32 ? (const T *)dense.f32.ptr : (const T *)dense.f64.ptr;
             const T *m2m = f32 ? (const T *)ops->m2m32.ptr : (const T *)ops->m2m64.ptr;
             const T *l2l = f32 ? (const T *)ops->l2l32.ptr : (const T *)ops->l2l64.ptr;
             const int16_t *lists = ctx->octlists.as<int16_t>();
@@ -1234,6 +1219,7 @@ vm_status adaptive_impl(vm_ctx *ctx, int64_t n64, const double *x, const double 
     const int n = int(n64);
     const int K = opts->periodic;
     if (vm_status st = ensure_tables(ctx); st != VM_OK) return st;
+    if (vm_status st = ensure_pair_table(ctx, 0); st != VM_OK) return st;
     OpSet *ops = nullptr;
     if (vm_status st = ensure_ops(ctx, p, &ops); st != VM_OK) return st;
     const double *tlat = nullptr;
@@ -1298,8 +1284,7 @@ vm_status adaptive_impl(vm_ctx *ctx, int64_t n64, const double *x, const double 
     const int nlev = int(lo.size()) - 1;
     // M2L by reflection orbits, all levels; beyond its kernels' reach the dense operators
     const bool ad_sym = m2l_sym_supported(p) && m2l_sym_fits(p, ncell, sizeof(double));
-    if (ad_sym)
-        if (vm_status st = ensure_sym_ops(ctx, ops, 0); st != VM_OK) return st;
+    if (vm_status st = ad_sym ? ensure_sym_ops(ctx, ops, 0) : ensure_m2l_ops(ctx, ops, 0, 0); st != VM_OK) return st;
 
     // --- leaves in particle order and the sorted records -----------------------
     VM_HIP(A.leaf_at.reserve(sizeof(int32_t) * size_t(n)), "alloc leaves");
@@ -1487,7 +1472,7 @@ vm_status adaptive_impl(vm_ctx *ctx, int64_t n64, const double *x, const double 
                                                  kAdSplitElems),
                        "adaptive M2L");
             } else {
-                VM_HIP(launch_translate_adaptive<double>(s, 0, p, kp, ops->m2l64.as<double>(), lists, M, L, 1, ad,
+                VM_HIP(launch_translate_adaptive<double>(s, 0, p, kp, ops->m2l[0][0].f64.as<double>(), lists, M, L, 1, ad,
                                                          A.tpart.as<double>(), kAdSplitElems),
                        "adaptive M2L");
             }
@@ -1701,17 +1686,17 @@ vm_status adjoint_impl(vm_ctx *ctx, int64_t n, const double *x, const double *al
     const int C = ncoef(p), kp = coef_stride(C);
     OpSet *ops = ctx->ops[p].get();
     if (vm_status e = ensure_adj_ops(ctx, ops); e != VM_OK) return e;
-    if (opts->truncation == VM_TRIANGULAR)
-        if (vm_status e = ensure_tri_ops(ctx, ops, 1); e != VM_OK) return e;
     const double *tlat_t = nullptr;
     if (K >= 2)
         if (vm_status e = ensure_lattice_t(ctx, p, K, &tlat_t); e != VM_OK) return e;
     // the adjoint M2L by reflection orbits where the forward one runs so
     const int lm2l = periodic ? 1 : 2;
     const bool use_sym = uniform_sym(opts, p, level);
+    const int tri = opts->truncation == VM_TRIANGULAR;
     const int64_t ncells = ((int64_t(1) << (3 * (level + 1))) - 1) / 7;
+    if (level >= lm2l)
+        if (vm_status e = use_sym ? ensure_sym_ops(ctx, ops, 1) : ensure_m2l_ops(ctx, ops, 1, tri); e != VM_OK) return e;
     if (use_sym) {
-        if (vm_status e = ensure_sym_ops(ctx, ops, 1); e != VM_OK) return e;
         VM_HIP(ctx->mcbuf.reserve((mixed ? sizeof(float) : sizeof(double)) * size_t(ncells + 1) * 3 *
                                   (16 * sym_layout(p).nblk)),
                "alloc class-major multipoles");
@@ -1740,9 +1725,8 @@ vm_status adjoint_impl(vm_ctx *ctx, int64_t n, const double *x, const double *al
             const bool f32 = sizeof(T) == 4;
             T *Mb = ctx->mbuf.as<T>(), *Lb = ctx->lbuf.as<T>();   // adjoints overwrite the forward state
             auto lev = [&](T *b, int l) { return b + size_t(((int64_t(1) << (3 * l)) - 1) / 7) * 3 * kp; };
-            const int tri = opts->truncation == VM_TRIANGULAR;
-            const T *m2lT = tri ? (f32 ? (const T *)ops->m2lTt32.ptr : (const T *)ops->m2lTt64.ptr)
-                                : (f32 ? (const T *)ops->m2lT32.ptr : (const T *)ops->m2lT64.ptr);
+            const OpSet::DenseM2L &dense = ops->m2l[1][tri];
+            const T *m2lT = f32 ? (const T *)dense.f32.ptr : (const T *)dense.f64.ptr;
             const T *m2mT = f32 ? (const T *)ops->m2mT32.ptr : (const T *)ops->m2mT64.ptr;
             const T *l2lT = f32 ? (const T *)ops->l2lT32.ptr : (const T *)ops->l2lT64.ptr;
             const T *tw = f32 ? (const T *)ops->t_w32.ptr : (const T *)ops->t_w64.ptr;
