@@ -240,20 +240,25 @@ constexpr double kInv4PiL2P = 0.079577471545947667884441881686257181;
 
 // u, grad, dalpha of sorted target gi from the near field of a P2P launch and
 // the far field uf, Jf: the P2P epilogue's operations in its order.
+// SHARES: with the near field in shares, whose loads are in flight together (4096
+// particles, 8 shares: L2P 28 us, 70 with one load after another; in one kernel with
+// the form for one share, that one took 88 instead of 76 us at 64^3).
+template <bool SHARES>
 __device__ __forceinline__ void combine_store(const NearCombine &c, size_t n, size_t gi, const double uf[3],
                                               const double Jf[9]) {
-    // the shares' loads in flight together (4096 particles, 8 shares: L2P 29 us, 70
-    // with one load after another)
     auto near = [&](int row) {
         const double *q = c.near + size_t(row) * n + gi;
-        if (c.shares == 1) return q[0];
-        double v[kP2PMaxShares];
+        if constexpr (!SHARES) {
+            return q[0];
+        } else {
+            double v[kP2PMaxShares];
 #pragma unroll
-        for (int k = 0; k < kP2PMaxShares; ++k) v[k] = q[size_t(k < c.shares ? k : 0) * 15 * n];
-        double s = v[0];
+            for (int k = 0; k < kP2PMaxShares; ++k) v[k] = q[size_t(k < c.shares ? k : 0) * 15 * n];
+            double s = v[0];
 #pragma unroll
-        for (int k = 1; k < kP2PMaxShares; ++k) s += k < c.shares ? v[k] : 0.0;
-        return s;
+            for (int k = 1; k < kP2PMaxShares; ++k) s += k < c.shares ? v[k] : 0.0;
+            return s;
+        }
     };
     const int oi = c.perm[gi];
     for (int b = 0; b < 3; ++b) c.u[b * n + oi] = near(b) * kInv4PiL2P + uf[b];
@@ -281,7 +286,7 @@ __device__ __forceinline__ void combine_store(const NearCombine &c, size_t n, si
         for (int b = 0; b < 3; ++b) c.dalpha[b * n + oi] = da[b];
 }
 
-template <typename T>
+template <typename T, bool SHARES>
 __global__ void __launch_bounds__(64) k_l2p(const typename PartOf<T>::type *__restrict__ parts,
                                             const int32_t *__restrict__ start, int n, int p, int kp,
                                             T inv_w, double su, double sj, DevTables tab,
@@ -381,7 +386,7 @@ __global__ void __launch_bounds__(64) k_l2p(const typename PartOf<T>::type *__re
         for (int b = 0; b < 3; ++b) uf[b] = double(u[b]) * su;
         for (int kk = 0; kk < 9; ++kk) Jf[kk] = double(J[kk]) * sj;
         if (nc.near) {
-            combine_store(nc, size_t(n), gi, uf, Jf);
+            combine_store<SHARES>(nc, size_t(n), gi, uf, Jf);
         } else {
             for (int b = 0; b < 3; ++b) far[size_t(b) * n + gi] = uf[b];
             for (int kk = 0; kk < 9; ++kk) far[size_t(3 + kk) * n + gi] = Jf[kk];
@@ -1061,7 +1066,8 @@ hipError_t launch_l2p(hipStream_t s, int nleaf, int n, const void *parts, const 
     const int C = (p + 1) * (p + 1);
     const size_t smem = sizeof(T) * (3 * size_t(C) + 12 * size_t(tab.nu) + 12);
     const double four_pi = 12.566370614359172953850573533118;
-    hipLaunchKernelGGL(k_l2p<T>, dim3(nleaf), dim3(64), smem, s, (const typename PartOf<T>::type *)parts,
+    const auto k = nc.near && nc.shares > 1 ? k_l2p<T, true> : k_l2p<T, false>;
+    hipLaunchKernelGGL(k, dim3(nleaf), dim3(64), smem, s, (const typename PartOf<T>::type *)parts,
                        start, n, p, kp, T(inv_w), 1.0 / (four_pi * w * w), 1.0 / (four_pi * w * w * w), tab,
                        l_leaf, far, lm, nc);
     return hipGetLastError();
