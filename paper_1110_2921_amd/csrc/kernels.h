@@ -483,14 +483,14 @@ bool m2l_sym_supported(int p);
 inline bool m2l_sym_fits(int p, int64_t ncell, size_t elem) {
     return (uint64_t(ncell) + 1) * 3 * 16 * sym_layout(p).nblk * elem <= uint64_t(1) << 32;
 }
-// M2L at `level` (FP32): dst[cell] (+)= sum over the interaction list, from the
+// M2L at `level` (FP32): dst[cell] = sum over the interaction list (rows < C), from the
 // class-major multipoles mc of the level (zero_cell: index of a zero cell,
 // relative to mc), operators ops (per octant, orbit-compact, offsets op_off
 // [8][57] in floats), orbit table `orbits`, output map row_std[16 nblk].
 // Splits over orbit ranges with partial sums in `part` as launch_translate.
 hipError_t launch_m2l_sym(hipStream_t s, int level, int periodic, int p, int kp, const float *mc, int64_t zero_cell,
                           const float *ops, const int32_t *op_off, const int32_t *orbits, const int16_t *row_std,
-                          float *dst, int accumulate, float *part, size_t part_elems);
+                          float *dst, float *part, size_t part_elems);
 
 // M2L of the levels lo .. hi (<= kSymMaxSmall) of a uniform tree by reflection
 // orbits in one launch: dst (locals of all levels, standard layout) is
@@ -503,9 +503,9 @@ hipError_t launch_m2l_orbits(hipStream_t s, int lo, int hi, int periodic, int p,
                              int64_t zero_cell, const T *ops, const int32_t *op_off, const int32_t *orbits,
                              const int16_t *row_std, T *dst);
 
-// Targets and sources of one level of an adaptive tree for the FP64 orbit
-// M2L: the level's cells grouped by octant, tcell[oct_base[o] ..] of oct_n[o]
-// cells (global cell indices); vtab[cell - cell0][189] the source cell of each
+// Targets and sources of an adaptive tree for the FP64 orbit M2L: the cells of all
+// levels grouped by octant, tcell[oct_base[o] ..] of oct_n[o] cells (global cell
+// indices); vtab[cell - cell0][189] the source cell of each
 // slot of the cell's octant list (-1: none), vslot[8][343] the slot of offset
 // d = source - target (index (dx+3) + 7 (dy+3) + 49 (dz+3)) in octant o's list;
 // split partials indexed by cell - part_cell0 over part_cells cells.
@@ -523,14 +523,14 @@ struct SymAdapt {
 // the offsets (doubles) of the slices of orbit o, column b at o nblk + b.
 hipError_t launch_m2l_sym64(hipStream_t s, int level, int periodic, int p, int kp, const double *mc,
                             int64_t zero_cell, const double *ops, const int32_t *sl_off, const int32_t *orbits,
-                            const int16_t *row_std, double *dst, int accumulate, double *part, size_t part_elems);
-// The same for one level of an adaptive tree: mc the class-major multipoles of
-// every cell (zero_cell: their count), dst the locals of every cell; the
-// level's orbit ranges split over workgroups (partials in `part`) when its
+                            const int16_t *row_std, double *dst, double *part, size_t part_elems);
+// The same for an adaptive tree, all levels in one launch: mc the class-major
+// multipoles of every cell (zero_cell: their count), added to dst, the locals of
+// every cell; the orbit ranges split over workgroups (partials in `part`) when the
 // tiles do not fill the chip.
 hipError_t launch_m2l_sym64_adaptive(hipStream_t s, int p, int kp, const double *mc, int64_t zero_cell,
                                      const double *ops, const int32_t *sl_off, const int32_t *orbits,
-                                     const int16_t *row_std, double *dst, int accumulate, const SymAdapt &ad,
+                                     const int16_t *row_std, double *dst, const SymAdapt &ad,
                                      double *part, size_t part_elems);
 
 }  // namespace vmfmm

@@ -83,8 +83,8 @@ __global__ void __launch_bounds__(kSymThreads) k_m2l_sym(int level, int periodic
                                                                     const int32_t *__restrict__ op_off,
                                                                     const int32_t *__restrict__ orbits,
                                                                     const int16_t *__restrict__ row_std,
-                                                                    float *__restrict__ dst, int accumulate,
-                                                                    int nsplit, float *__restrict__ part) {
+                                                                    float *__restrict__ dst, int nsplit,
+                                                                    float *__restrict__ part) {
     typedef float f4 __attribute__((ext_vector_type(4)));
     constexpr SymLayout SL = sym_layout(P);
     constexpr int NB = SL.nblk, KC = 16 * NB;
@@ -262,7 +262,7 @@ __global__ void __launch_bounds__(kSymThreads) k_m2l_sym(int level, int periodic
             const int e = 4 * h + r;
             if (e < SL.bnv[A]) {
                 float *o = out + srow[16 * A + e];
-                *o = (accumulate && !split) ? *o + acc[A][r] : acc[A][r];
+                *o = acc[A][r];
             }
         }
     });
@@ -286,7 +286,7 @@ __global__ void __launch_bounds__(kSymThreads) k_m2l_sym64(int level, int period
                                                            const int32_t *__restrict__ sl_off,
                                                            const int32_t *__restrict__ orbits,
                                                            const int16_t *__restrict__ row_std,
-                                                           double *__restrict__ dst, int accumulate, int nsplit,
+                                                           double *__restrict__ dst, int nsplit,
                                                            double *__restrict__ part, SymAdapt ad) {
     typedef double d2 __attribute__((ext_vector_type(2)));
     typedef double d4 __attribute__((ext_vector_type(4)));
@@ -501,7 +501,7 @@ __global__ void __launch_bounds__(kSymThreads) k_m2l_sym64(int level, int period
             const int e = h + 4 * r;   // the FP64 MFMA's output row of lane group h, element r
             if (e < SL.bnv[A]) {
                 double *o = out + srow[16 * A + e];
-                *o = (accumulate && !split) ? *o + acc[A][r] : acc[A][r];
+                *o = (AD && !split) ? *o + acc[A][r] : acc[A][r];
             }
         }
     });
@@ -805,7 +805,7 @@ static int orbit_splits(int tiles, size_t per_split, size_t part_elems) {
 template <int P>
 hipError_t m2l_sym64(hipStream_t s, int level, int periodic, int kp, const double *mc, int64_t zero_cell,
                      const double *ops, const int32_t *sl_off, const int32_t *orbits, const int16_t *row_std,
-                     double *dst, int accumulate, double *part, size_t part_elems) {
+                     double *dst, double *part, size_t part_elems) {
     if (level < 1) return hipErrorInvalidValue;
     constexpr SymLayout SL = sym_layout(P);
     constexpr int KC = 16 * SL.nblk;
@@ -817,26 +817,26 @@ hipError_t m2l_sym64(hipStream_t s, int level, int periodic, int kp, const doubl
     double *pbuf = nsplit > 1 ? part : nullptr;
     const dim3 grid{unsigned(tiles), unsigned(nsplit)};
     hipLaunchKernelGGL((k_m2l_sym64<P, false>), grid, dim3(kSymThreads), smem, s, level, periodic, kp, mc,
-                       uint32_t(zero_cell * 3 * KC), ops, sl_off, orbits, row_std, dst, accumulate, nsplit, pbuf,
+                       uint32_t(zero_cell * 3 * KC), ops, sl_off, orbits, row_std, dst, nsplit, pbuf,
                        SymAdapt());
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || nsplit == 1) return e;
-    return launch_split_reduce64(s, level, kp, SL.C, nsplit, pbuf, dst, accumulate);
+    return launch_split_reduce64(s, level, kp, SL.C, nsplit, pbuf, dst, 0);
 }
 
 hipError_t launch_m2l_sym64(hipStream_t s, int level, int periodic, int p, int kp, const double *mc,
                             int64_t zero_cell, const double *ops, const int32_t *sl_off, const int32_t *orbits,
-                            const int16_t *row_std, double *dst, int accumulate, double *part, size_t part_elems) {
+                            const int16_t *row_std, double *dst, double *part, size_t part_elems) {
     return with_degree(p, [&](auto pc) {
         return m2l_sym64<decltype(pc)::value>(s, level, periodic, kp, mc, zero_cell, ops, sl_off, orbits, row_std, dst,
-                                              accumulate, part, part_elems);
+                                              part, part_elems);
     });
 }
 
 template <int P>
 hipError_t m2l_sym64_adaptive(hipStream_t s, int kp, const double *mc, int64_t zero_cell, const double *ops,
                               const int32_t *sl_off, const int32_t *orbits, const int16_t *row_std, double *dst,
-                              int accumulate, const SymAdapt &ad_in, double *part, size_t part_elems) {
+                              const SymAdapt &ad_in, double *part, size_t part_elems) {
     constexpr SymLayout SL = sym_layout(P);
     constexpr int KC = 16 * SL.nblk;
     if (!m2l_sym_fits(P, zero_cell, sizeof(double))) return hipErrorInvalidValue;
@@ -851,22 +851,21 @@ hipError_t m2l_sym64_adaptive(hipStream_t s, int kp, const double *mc, int64_t z
     double *pbuf = nsplit > 1 ? part : nullptr;
     const size_t smem = sizeof(double) * size_t(kRing) * size_t(16 * SL.C + 32);
     hipLaunchKernelGGL((k_m2l_sym64<P, true>), dim3(unsigned(grid), unsigned(nsplit)), dim3(kSymThreads), smem, s,
-                       0, 0, kp, mc, uint32_t(zero_cell * 3 * KC), ops, sl_off, orbits, row_std, dst, accumulate,
+                       0, 0, kp, mc, uint32_t(zero_cell * 3 * KC), ops, sl_off, orbits, row_std, dst,
                        nsplit, pbuf, ad);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || nsplit == 1) return e;
     const int64_t nelem = int64_t(ad.part_cells) * 3 * kp;
-    return launch_split_reduce64_n(s, nelem, kp, SL.C, nsplit, pbuf, dst + size_t(ad.part_cell0) * 3 * kp,
-                                   accumulate);
+    return launch_split_reduce64_n(s, nelem, kp, SL.C, nsplit, pbuf, dst + size_t(ad.part_cell0) * 3 * kp, 1);
 }
 
 hipError_t launch_m2l_sym64_adaptive(hipStream_t s, int p, int kp, const double *mc, int64_t zero_cell,
                                      const double *ops, const int32_t *sl_off, const int32_t *orbits,
-                                     const int16_t *row_std, double *dst, int accumulate, const SymAdapt &ad,
+                                     const int16_t *row_std, double *dst, const SymAdapt &ad,
                                      double *part, size_t part_elems) {
     return with_degree(p, [&](auto pc) {
-        return m2l_sym64_adaptive<decltype(pc)::value>(s, kp, mc, zero_cell, ops, sl_off, orbits, row_std, dst,
-                                                       accumulate, ad, part, part_elems);
+        return m2l_sym64_adaptive<decltype(pc)::value>(s, kp, mc, zero_cell, ops, sl_off, orbits, row_std, dst, ad,
+                                                       part, part_elems);
     });
 }
 
@@ -907,7 +906,7 @@ template hipError_t launch_m2l_orbits<double>(hipStream_t, int, int, int, int, i
 template <int P>
 hipError_t m2l_sym32(hipStream_t s, int level, int periodic, int kp, const float *mc, int64_t zero_cell,
                      const float *ops, const int32_t *op_off, const int32_t *orbits, const int16_t *row_std,
-                     float *dst, int accumulate, float *part, size_t part_elems) {
+                     float *dst, float *part, size_t part_elems) {
     if (level < 1) return hipErrorInvalidValue;
     constexpr SymLayout SL = sym_layout(P);
     constexpr int KC = 16 * SL.nblk;
@@ -919,18 +918,18 @@ hipError_t m2l_sym32(hipStream_t s, int level, int periodic, int kp, const float
     float *pbuf = nsplit > 1 ? part : nullptr;
     const dim3 grid{unsigned(tiles), unsigned(nsplit)};
     hipLaunchKernelGGL(k_m2l_sym<P>, grid, dim3(kSymThreads), smem, s, level, periodic, kp, mc,
-                       uint32_t(zero_cell * 3 * KC), ops, op_off, orbits, row_std, dst, accumulate, nsplit, pbuf);
+                       uint32_t(zero_cell * 3 * KC), ops, op_off, orbits, row_std, dst, nsplit, pbuf);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || nsplit == 1) return e;
-    return launch_split_reduce(s, level, kp, SL.C, nsplit, pbuf, dst, accumulate);
+    return launch_split_reduce(s, level, kp, SL.C, nsplit, pbuf, dst, 0);
 }
 
 hipError_t launch_m2l_sym(hipStream_t s, int level, int periodic, int p, int kp, const float *mc, int64_t zero_cell,
                           const float *ops, const int32_t *op_off, const int32_t *orbits, const int16_t *row_std,
-                          float *dst, int accumulate, float *part, size_t part_elems) {
+                          float *dst, float *part, size_t part_elems) {
     return with_degree(p, [&](auto pc) {
         return m2l_sym32<decltype(pc)::value>(s, level, periodic, kp, mc, zero_cell, ops, op_off, orbits, row_std, dst,
-                                              accumulate, part, part_elems);
+                                              part, part_elems);
     });
 }
 

@@ -272,10 +272,8 @@ inline int p2p_blocks(int nleaf, int ntarget, int slots) {
     return std::max(1, std::min(slots / nleaf, (ntarget / nleaf + 63) / 64));
 }
 
-// Leaves a wave or a workgroup takes (powers of two, as the leaf count).
-// Split: enough leaves per workgroup to make the table's copy into LDS (about 2
-// us) small beside them (a leaf 100 us), few enough to keep the launch's last
-// workgroups short.
+// Leaves a workgroup takes: one where its waves split it (leaf counts are powers of
+// 8, so at most 4096 leaves here, a few workgroups a compute unit), else one a wave.
 struct P2PShape {
     bool split;
     dim3 grid;
@@ -286,7 +284,7 @@ struct P2PShape {
 inline P2PShape p2p_shape(const P2PArgs &a, int slots, int table_bytes) {
     P2PShape s;
     s.split = a.nleaf < kP2PSplitLeaves;
-    const int run = s.split ? (a.nleaf >= 8192 ? 4 : 1) : kP2PWaves;
+    const int run = s.split ? 1 : kP2PWaves;
     s.grid = dim3(unsigned(a.nleaf / run), unsigned(p2p_blocks(a.nleaf, a.n, slots)),
                   a.near ? unsigned(a.shares) : 1u);
     s.smem = size_t(table_bytes) + (s.split ? sizeof(double) * kRedDoubles : 0);

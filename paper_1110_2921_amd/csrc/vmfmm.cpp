@@ -865,11 +865,11 @@ vm_status sym_m2l(vm_ctx *ctx, int lo, int hi, int periodic, int p, int kp, cons
         const size_t elems = ctx->trpart.bytes / sizeof(T);
         if constexpr (sizeof(T) == 4)
             VM_HIP(launch_m2l_sym(s, l, periodic, p, kp, mc + size_t(base) * 3 * kc, ncells - base, op, off, orb, row,
-                                  out + size_t(base) * 3 * kp, 0, part, elems),
+                                  out + size_t(base) * 3 * kp, part, elems),
                    "M2L");
         else
             VM_HIP(launch_m2l_sym64(s, l, periodic, p, kp, mc + size_t(base) * 3 * kc, ncells - base, op, off, orb,
-                                    row, out + size_t(base) * 3 * kp, 0, part, elems),
+                                    row, out + size_t(base) * 3 * kp, part, elems),
                    "M2L");
     }
     return VM_OK;
@@ -1468,7 +1468,7 @@ vm_status adaptive_impl(vm_ctx *ctx, int64_t n64, const double *x, const double 
                 sa.part_cells = ad.part_cells;
                 VM_HIP(launch_m2l_sym64_adaptive(s, p, kp, A.mc.as<double>(), ncell, ops->sym[0].ops64.as<double>(),
                                                  ops->sym[0].sl64.as<int32_t>(), ops->sym_orb.as<int32_t>(),
-                                                 ops->sym_row.as<int16_t>(), L, 1, sa, A.tpart.as<double>(),
+                                                 ops->sym_row.as<int16_t>(), L, sa, A.tpart.as<double>(),
                                                  kAdSplitElems),
                        "adaptive M2L");
             } else {
