@@ -208,7 +208,8 @@ def measured_tree_bytes(workload, precision):
         return None
     ks = d["kernels"]
     evals = ks["k_keys"]["dispatches"]          # one key pass per evaluation
-    return sum(ks[k]["hbm_bytes_per_launch"] * ks[k]["dispatches"] / evals for k in TREE_KERNELS if k in ks)
+    return sum(v["hbm_bytes_per_launch"] * v["dispatches"] / evals for k, v in ks.items()
+               if k.split("<")[0] in TREE_KERNELS)
 
 
 def direct_at(x, a, sigma, box_len, targets):
@@ -437,7 +438,7 @@ def main():
                 "peak": PEAKS["mfma_f32_tflops" if f32 else "mfma_f64_tflops"], "unit": "TFLOP/s",
                 "traffic": m2l_traffic, "traffic_unit": "bytes per evaluation",
                 "algorithmic_bytes_per_eval": m2l_alg_bytes, "launches_per_eval": m2l_launch}
-    sym_name = f"k_m2l_sym<{w.p}>" if f32 else f"k_m2l_sym64<{w.p}>"
+    sym_name = f"k_m2l_sym<{w.p}>" if f32 else f"k_m2l_sym64<{w.p},false>"
     fin = measured_finest_launch(w.name, args.precision, sym_name) if orbit else None
     if fin:
         roof_m2l["finest_level_launch"] = {"kernel": sym_name, "grid_size": fin[0], "hbm_bytes": fin[1],

@@ -32,3 +32,15 @@ def test_every_kernel_of_the_library_is_summarised(tmp_path, monkeypatch):
     per_kernel = 1024 * (2 * 8.0 + 8.0)
     got = bench.measured_phase_bytes("toy", "mixed", ("k_m2l_sym<", "k_m2l_orbits<float", "k_sym_pack<float>"))
     assert got == 3 * per_kernel
+
+
+def test_tree_bytes_count_template_instances(tmp_path, monkeypatch):
+    """The radix passes' kernels are templates; their bytes belong to the tree's."""
+    one = {"dispatches": 4, "hbm_bytes_per_launch": 3.0}
+    body = {"sources_sha256": R.sources_sha256(), "kernels": {
+        "k_keys": {"dispatches": 2, "hbm_bytes_per_launch": 5.0}, "k_radix_hist<16>": one, "k_radix_scatter<4>": one,
+        "k_permute": one, "k_p2p32<false,true>": one}}
+    os.makedirs(tmp_path / "profiles")
+    (tmp_path / "profiles" / "hbm_traffic_toy_mixed.txt").write_text(json.dumps(body))
+    monkeypatch.setattr(bench, "ROOT", str(tmp_path))
+    assert bench.measured_tree_bytes("toy", "mixed") == 5.0 + 3 * 6.0
