@@ -86,8 +86,8 @@ hipError_t launch_p2m(hipStream_t s, int nleaf, const void *parts, const int32_t
 
 // With `near` set, L2P adds the far field it evaluates to the near field a P2P
 // launch stored there (P2PArgs::near, sorted order) and writes u, grad and
-// dalpha in caller order, exactly as the P2P epilogue combines them; `far` is
-// then not written.
+// dalpha in caller order with the P2P epilogue's operations; `far` is then not
+// written.
 struct NearCombine {
     const double *near = nullptr;    // [shares][15][n], the shares added in order
     int shares = 1;

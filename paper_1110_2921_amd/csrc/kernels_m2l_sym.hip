@@ -514,12 +514,15 @@ __global__ void __launch_bounds__(kSymThreads) k_m2l_sym64(int level, int period
 // eighth orbit each, with the operator blocks read from L2 straight into the
 // MFMA's A registers and the next step's operator blocks and sources in flight
 // during the current step's MFMAs; the waves' sums meet in LDS, in wave order.
-// Bound by the vector L1 (each wave reads its own operator blocks, 64 B a cycle and
-// CU), not by MFMA; two shares of the row blocks put twice the waves on the few
-// tiles (one share: 106 against 88 us, three: 145, FP32 levels 1 to 3).
-// Levels 1 to 3, periodic: p = 10 FP32 88 us, FP64 269 us, p = 8 FP64 136 us; the
-// dense operators, 189 offsets split over workgroups and their partial sums
-// added by a second launch per level, took 510, 497 and 432 us.
+// What it waits for is loads, not MFMA: in FP32 a wave's step fetches 8 KB of sources
+// (of an orbit's eight slots 3.4 on average are members, the others read the zero
+// cell) and, at p = 10, 4 to 5 KB of its own operator blocks.  Two shares of the row
+// blocks put twice the waves on the few tiles (one share: 106 against 88 us, three: 145,
+// FP32 levels 1 to 3).
+// Levels 1 to 3, periodic: p = 10 FP32 88 us, FP64 170 us, p = 8 83 and 144 us, p = 6 80
+// and 91 us; the dense operators, 189 offsets split over workgroups and their partial
+// sums added by a second launch per level, took 510, 497 (p = 10) and 432 us (p = 8
+// FP64).
 // FP32: a step is a k block (four k steps); FP64: half a block.
 template <typename T> struct Step;
 template <> struct Step<float> {
@@ -740,6 +743,9 @@ __global__ void __launch_bounds__(kOrbThreads) k_m2l_orbits(OrbLevels lv, int pe
 
 }  // namespace
 
+// The degrees of the workloads; each costs the build four more kernels.  The class
+// layout would carry the other degrees below 11 as well; at p = 12 the FP64 kernel's
+// ring of eight slices (175 KB) exceeds the LDS.
 bool m2l_sym_supported(int p) { return p == 6 || p == 8 || p == 10; }
 
 template <typename T>

@@ -1070,6 +1070,11 @@ vm_status fmm_impl(vm_ctx *ctx, int64_t n, const double *x, const double *alpha,
                            "L2L");
                 }
                 if (!sym) {
+                    // beyond p = 10 the operators of the levels that fill the chip stream from L2
+                    // and lose more beside P2P than the overlap gives (p = 12, level 4, 64
+                    // particles a leaf, mixed: 3.95 ms an evaluation beside P2P, 3.47 after it;
+                    // p = 7: 1.90 and 1.93); levels 2 and 3 fill gaps beside it
+                    if (p > 10 && l == 4) VM_HIP(hipStreamWaitEvent(s, ctx->ev_join, 0), "join");
                     Timed tm(ctx, VM_PH_M2L);
                     VM_HIP(launch_translate<T>(s, 0, l, periodic, p, kp, m2l, lists, offs, lev(M, l), lev(L, l),
                                                have_parent ? 1 : 0, ctx->trpart.as<T>(), ctx->trpart.bytes / sizeof(T),
