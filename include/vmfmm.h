@@ -454,7 +454,7 @@ vm_status vm_tune_level(vm_ctx *ctx, int64_t n, const double *x, const double *a
  * milliseconds and the number of launches of each phase (at most 32768
  * launches are recorded); it synchronises the stream.  vm_gauss_sum and
  * vm_rbf_solve add their tree build to VM_PH_TREE and their own work to the
- * last two phases.  Phases, in launch order:
+ * last two phases.  Phases:
  */
 enum {
     VM_PH_TREE = 0,   /* keys, radix sort passes, leaf ranges, permutation */
