@@ -678,13 +678,10 @@ k_p2p64_list(P2PArgs a, int nitem, const int2 *__restrict__ items, const int32_t
                     if (E == 64) pol.uniform(parts, m.js, m.je, tx, ty, tz, A);
                     else pol.grouped(parts, m.js + grp, m.je, ng, tx, ty, tz, A);
                 }
-                auto sum = [&](auto kc) {
-                    double v = pol.template value<decltype(kc)::value>(A);
-                    for (int o = E; o < 64; o <<= 1) v += __shfl_xor(v, o);
-                    return v;
-                };
+                auto value = [&](auto kc) { return pol.template value<decltype(kc)::value>(A); };
                 for_rows([&](auto rc) {
-                    wave_round<decltype(rc)::value>(red, sum, [&](int r, double v) { fin[r * 64 + lane] = v; });
+                    wave_round<decltype(rc)::value>(red, value,
+                                                    [&](int r, double v) { fin[r * 64 + lane] = group_sum(v, E); });
                 }, std::make_integer_sequence<int, kNearRows / kRedRows>{});
                 if (wave == 0) finish(a, gi, write, [&](int r) { return fin[64 * r + lane]; });
             }
