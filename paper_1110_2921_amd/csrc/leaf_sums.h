@@ -223,12 +223,15 @@ __device__ __forceinline__ void p2p_leaves(const P2PArgs &a, const typename POL:
                 if (E == 64) pol.uniform(parts, js, je, tx, ty, tz, A);
                 else pol.grouped(parts, js + grp, je, ng, tx, ty, tz, A);
             }
-            auto value = [&](auto kc) { return pol.template value<decltype(kc)::value>(A); };
+            auto sum = [&](auto kc) {   // SPLIT: the lane's share
+                const double x = pol.template value<decltype(kc)::value>(A);
+                return SPLIT ? x : group_sum(x, E);
+            };
             const bool all = a.grad || a.dalpha;
             if constexpr (!SPLIT) {
                 if (a.near) {
                     auto put = [&](auto kc) {
-                        const double x = group_sum(value(kc), E);
+                        const double x = sum(kc);
                         if (write) a.near[size_t(decltype(kc)::value) * n + gi] = x;
                     };
                     for_rows(put, std::make_integer_sequence<int, 3>{});
@@ -237,14 +240,14 @@ __device__ __forceinline__ void p2p_leaves(const P2PArgs &a, const typename POL:
                                  std::make_integer_sequence<int, kNearRows - 3>{});
                 } else {
                     double f[kNearRows];
-                    for_rows([&](auto kc) { f[decltype(kc)::value] = group_sum(value(kc), E); },
+                    for_rows([&](auto kc) { f[decltype(kc)::value] = sum(kc); },
                              std::make_integer_sequence<int, kNearRows>{});
                     finish(a, gi, write, [&](int r) { return f[r]; });
                 }
             } else {
                 // the waves' sums first, kRedRows rows a round, then the lane groups'
                 auto round = [&](auto rc) {
-                    wave_round<decltype(rc)::value>(red, value, [&](int r, double x) {
+                    wave_round<decltype(rc)::value>(red, sum, [&](int r, double x) {
                         x = group_sum(x, E);
                         if (!a.near) fin[r * 64 + lane] = x;
                         else if (write) a.near[(size_t(blockIdx.z) * kNearRows + r) * n + gi] = x;
