@@ -345,7 +345,7 @@ hipError_t launch_ad_permute(hipStream_t s, const AdTreeView &t, int n, const do
 // list k of cell c at off[k ncell + c] ..) and the M2L table (row c - vcell0)
 hipError_t launch_ad_traverse(hipStream_t s, const AdTreeView &t, const AdLists &ls, int l, int off, int ncl,
                               int pass, int vcell0, int ncell);
-// P2L: local expansions of the cells [off, off + ncl) (holding L2L and M2L)
+// P2L: local expansions of the cells [off, off + ncl) (holding their M2L)
 // += the particles of the source leaves of their P2L lists
 hipError_t launch_ad_p2l(hipStream_t s, const AdTreeView &t, const AdLists &ls, int off, int ncl, int ncell, int p,
                          int kp, const DevTables &tab, const Part64 *parts, double *L);

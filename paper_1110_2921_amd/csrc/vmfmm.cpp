@@ -1,6 +1,6 @@
 // Host driver of the C ABI declared in include/vmfmm.h: argument checks,
 // workspace and operator caches, and the launch sequence of one evaluation
-// (tree -> P2M -> M2M -> lattice -> L2L/M2L per level -> L2P -> P2P).
+// (tree -> P2M -> M2M -> lattice -> M2L -> L2L -> L2P, P2P beside them).
 #include "../../include/vmfmm.h"
 
 #include <hip/hip_runtime.h>
@@ -1216,7 +1216,7 @@ vm_status ensure_ad_tables(vm_ctx *ctx, int p) {
 
 // Adaptive hybrid treecode-FMM (Sec. 3.2), FP64: tree from the particles
 // sorted at max_level, dual traversal into P2P / M2L / M2P / P2L lists, then
-// P2M, M2M, lattice, L2L + M2L + P2L per level, L2P + M2P, P2P.
+// P2M, M2M, lattice, M2L and P2L of all levels, L2L, L2P + M2P, P2P.
 vm_status adaptive_impl(vm_ctx *ctx, int64_t n64, const double *x, const double *alpha, double sigma, int p,
                         int ncrit, int max_level, const vm_opts *opts, double *u, double *dalpha_dt, double *grad) {
     hipStream_t s = ctx->stream;
